@@ -300,7 +300,6 @@ struct PoissonWS {
   double *vol = nullptr;   // its cell volumes (fine layout, FP64)
   double *met_w = nullptr; // its cell widths per level and direction (x then y, level after level)
   double volume = 0.0;     // its domain area (the weight of the solution mean)
-  void *met_tab = nullptr; // its coarse-level spacing tables (MG precision)
   Lay lay;                 // fine layout (FP64 CG vectors)
   Bnd bnd;
   int nlev, lc;            // MG levels; first level handled by the coarse kernel
@@ -310,7 +309,6 @@ struct PoissonWS {
   double *x, *r[2], *p[2], *q;
   int cgcg;                // single-reduction (Chronopoulos-Gear) CG in FP64 mode
   int block_pcg;           // the whole solve in one workgroup (finest level <= kCoarseCells)
-  double *blk;             // its scratch (face coefficients, p, s)
   double tol2;             // rtol^2 of the solve in progress
   double *w, *s[2];        // its A u and s = A p vectors
   void *z[2];              // preconditioned residuals in MG precision
@@ -327,7 +325,9 @@ struct PoissonWS {
   int vtx[kMaxLev], vty[kMaxLev];  // 2D tile of the variable-coefficient level kernels
   double *rho64;           // finest-level density (FP64, fine layout)
   void *rho[kMaxLev];      // density per level in MG precision (level 0 aliases rho64 in FP64)
-  void *rho_c;             // densities of the coarse-kernel levels, packed as its LDS
+  void *geo;               // block geometry of the coarse-kernel levels
+  void *ccf;               // face coefficients of the coarse-kernel levels, by block (MG precision)
+  double *ccd;             // those of the finest level in FP64 (one-workgroup solve, mixed precision)
   void *pinv_vc;           // pseudo-inverse of the coarsest variable-coefficient operator
   void *cf[kMaxLev][3];    // tiled 2D levels: west-face and south-face beta, 1/diagonal of L
   hipEvent_t *tev;         // in-step timing of the finest down kernel: event pairs
@@ -340,10 +340,11 @@ struct PoissonWS {
 // arrays. Returns false if the grid does not coarsen to <= kMaxCoarsest cells.
 bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, const double h[3], int mixed, int flexible,
                   int nu, int vc_cap, std::string *err);
-// Host-side set-up of the coarsest-level pseudo-inverse (after carving).
+// Set-up of the coarse-kernel levels' block geometry and (on the host) of
+// the coarsest-level pseudo-inverse (after carving).
 hipError_t poisson_setup(hipStream_t st, PoissonWS &ws, const double h[3]);
-// The same pseudo-inverse built on the device (one block, Gauss-Jordan in
-// LDS); needs a coarsest level of <= kVcCoarsest cells
+// The same with the pseudo-inverse built on the device (one block,
+// Gauss-Jordan in LDS); needs a coarsest level of <= kVcCoarsest cells
 // (hipErrorInvalidValue otherwise).
 hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws);
 // Solve A x = b for the zero-mean x (A P = sum_d delta_1 delta_1 P with
@@ -357,15 +358,15 @@ hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const d
                          int maxit, int expect_iters, int *iters, double *relres, int *converged,
                          SolveLog *log = nullptr);
 // Prepares a variable-coefficient solve from the density in ws.rho64 (fine
-// layout): the density on every level (2^d-cell averages), the packed
-// coarse-level densities and the coarsest pseudo-inverse. Sets
+// layout): the density on every level (2^d-cell averages), the coarse
+// levels' face coefficients and the coarsest pseudo-inverse. Sets
 // sc->rho_bad when a density is not positive and finite. The caller then
 // sets ws.vc for the solve.
 hipError_t poisson_set_beta(hipStream_t st, PoissonWS &ws);
 // Stretched 2D grid (ws.met, planned with vc_cap): from the finest cell
 // widths wx (n[0]) and wy (n[1]) (host arrays), every level's cell ratios
-// dx/dy, the finest cell volumes, the packed coarse-level ratios and the
-// coarsest pseudo-inverse; leaves ws.vc set for every later solve.
+// dx/dy, the finest cell volumes, the coarse levels' face coefficients and
+// the coarsest pseudo-inverse; leaves ws.vc set for every later solve.
 hipError_t poisson_set_metric(hipStream_t st, PoissonWS &ws, const double *wx, const double *wy);
 // One launch of a solver kernel class for timing (see lm_bench_kernel);
 // the caller has cleared sc->done. Returns hipErrorInvalidValue for an

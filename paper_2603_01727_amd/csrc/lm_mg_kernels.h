@@ -1,11 +1,8 @@
-// Multigrid kernels of the Poisson preconditioner that work out of LDS:
-//  - fused 2D tile kernels with temporal blocking (one launch per level and
-//    direction of the V-cycle), and
-//  - the one-block coarse V-cycle over all levels of at most kCoarseCells
-//    cells, with the dense pseudo-inverse on the coarsest grid.
-// Each comes in the constant-coefficient form (beta = 1) and, with VC, in
-// the variable-coefficient form beta = 1/rho_f (face_beta), whose level
-// operators are rediscretised from the level's density (2^d-cell averages).
+// Fused 2D multigrid level kernels that work out of LDS tiles with temporal
+// blocking (one launch per level and direction of the V-cycle), in the
+// constant-coefficient form (beta = 1) and, with VC, in the
+// variable-coefficient form beta = 1/rho_f (face_beta), whose level operators
+// are rediscretised from the level's density (2^d-cell averages).
 // Included by lm_solver.hip only.
 #pragma once
 
@@ -619,480 +616,6 @@ __global__ void __launch_bounds__(kBlock) k_mg_up2d(Up2DArgs<T> a) {
       a.part_rz[blockIdx.x] = v3[0];
       a.part_rz[a.np + blockIdx.x] = v3[1];
       a.part_rz[2 * a.np + blockIdx.x] = v3[2];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// One-block coarse V-cycle in LDS
-// ---------------------------------------------------------------------------
-constexpr int kCoarseLds = 5504;  // cells of all coarse levels together (4096 + 1024 + ... in 2D)
-constexpr int kCoarseLoads = 4;   // cells per thread of the first coarse level (<= 4 x 1024)
-constexpr int kCoarseLev = 8;     // coarse levels handled by the one-block kernel, at most
-
-template <typename T>
-struct CoarseArgs {
-  int l0, nlev, nu;
-  Bnd B;
-  int n[kMaxLev][3];
-  int off[kMaxLev];        // LDS offset of each level (compact, x fastest)
-  int lg[kMaxLev][2];      // log2(n[0]/2), log2(n[1]) or -1 when not a power of two
-  Ih2<T> ih2[kMaxLev];
-  T idg[kCoarseLev][8];    // 1/diagonal of coarse level l0 + q, by neighbour code
-  Lay L0;                  // global layout of level l0
-  const void *b0;          // global right-hand side of level l0
-  int b0_double;
-  T *x0;                   // global output: correction of level l0
-  const T *pinv;           // dense pseudo-inverse of the coarsest level
-  const T *rho_c;          // variable coefficients: densities of levels l0.., packed at off[]
-  int met = 0;             // stretched 2D grid: rho_c holds dx/dy (face_coef)
-  // stretched 2D grid: per level l >= l0 at toff[l] the cell widths wx[n0],
-  // wy[n1] and the face factors gx[n0], gy[n1] (g = 2 / (sum of the two
-  // widths across the face; the last face wraps when periodic, else 0)
-  const T *mtab = nullptr;
-  int mtab_n = 0;
-  int toff[kMaxLev];
-};
-
-// Stretched 2D grid: the four face coefficients (west, east, south, north)
-// of cell (i, j) of a level from its 1D tables: an x-face carries the
-// cell height over the distance between the two centres, dy_j 2/(dx_a +
-// dx_b), a y-face dx_i 2/(dy_a + dy_b), each times the level's scale.
-// Faces on a wall get 0 from the table.
-template <typename T>
-__device__ inline void m_faces(const T *tab, int toff, int n0, int n1, int i, int j, T ihx, T ihy, T cf[4]) {
-  const T *wx = tab + toff, *wy = wx + n0, *gx = wy + n1, *gy = gx + n0;
-  const int im = i > 0 ? i - 1 : n0 - 1, jm = j > 0 ? j - 1 : n1 - 1;
-  const T ay = ihx * wy[j], ax = ihy * wx[i];
-  cf[0] = ay * gx[im];
-  cf[1] = ay * gx[i];
-  cf[2] = ax * gy[jm];
-  cf[3] = ax * gy[j];
-}
-
-template <int DIM, typename T>
-__device__ inline void c_decode(const int n[3], int t, int &i, int &j, int &k) {
-  const int n0 = n[0], n1 = n[1];
-  int row;
-  if ((n0 & (n0 - 1)) == 0) {
-    i = t & (n0 - 1);
-    row = t >> __builtin_ctz(n0);
-  } else {
-    row = t / n0;
-    i = t - row * n0;
-  }
-  if (DIM == 3) {
-    if ((n1 & (n1 - 1)) == 0) {
-      j = row & (n1 - 1);
-      k = row >> __builtin_ctz(n1);
-    } else {
-      k = row / n1;
-      j = row - k * n1;
-    }
-  } else {
-    j = row;
-    k = 0;
-  }
-}
-
-// Sum of the neighbours of cell c = (i, j, k), each scaled by 1/h_d^2, with
-// no branches: a missing neighbour (a non-periodic side) is read at c and
-// weighted 0. code gets bit d set when both neighbours along d exist; the
-// diagonal of the cell is sum_d ih2[d] (1 + bit d), tabulated as 1/diag.
-template <int DIM, typename T>
-__device__ inline T c_nbs(const int n[3], const Bnd &B, const T ih2[3], const T *x, int i, int j, int k, int c,
-                          int &code) {
-  const int q[3] = {i, j, k};
-  const int st[3] = {1, n[0], n[0] * n[1]};
-  T v[2 * DIM], w[2 * DIM];
-  code = 0;
-#pragma unroll
-  for (int d = 0; d < DIM; ++d) {
-    const bool per = B.periodic[d] != 0;
-    const bool lo = q[d] > 0, hi = q[d] + 1 < n[d];
-    const int cm = lo ? c - st[d] : (per ? c + (n[d] - 1) * st[d] : c);
-    const int cp = hi ? c + st[d] : (per ? c - (n[d] - 1) * st[d] : c);
-    v[2 * d] = x[cm];
-    v[2 * d + 1] = x[cp];
-    w[2 * d] = (lo || per) ? T(1) : T(0);
-    w[2 * d + 1] = (hi || per) ? T(1) : T(0);
-    code |= ((lo || per) && (hi || per)) ? (1 << d) : 0;
-  }
-  T nbs = T(0);
-#pragma unroll
-  for (int d = 0; d < DIM; ++d) nbs += ih2[d] * (w[2 * d] * v[2 * d] + w[2 * d + 1] * v[2 * d + 1]);
-  return nbs;
-}
-
-// q = t / n, r = t % n with a shift when lg >= 0 (n = 2^lg).
-__device__ inline int c_divmod(int t, int n, int lg, int &r) {
-  if (lg >= 0) {
-    r = t & (n - 1);
-    return t >> lg;
-  }
-  const int q = t / n;
-  r = t - q * n;
-  return q;
-}
-
-// Cell of colour `color` number t of level l (even n[0]): the cells of one
-// colour are enumerated directly, i = 2m + ((colour + j + k) & 1).
-template <int DIM, typename T>
-__device__ inline int c_colour_cell(const CoarseArgs<T> &a, int l, int color, int t, int &i, int &j, int &k) {
-  const int *n = a.n[l];
-  int m;
-  k = 0;
-  const int row = c_divmod(t, n[0] >> 1, a.lg[l][0], m);
-  if (DIM == 3)
-    k = c_divmod(row, n[1], a.lg[l][1], j);
-  else
-    j = row;
-  i = 2 * m + ((color + j + k) & 1);
-  return i + n[0] * (j + n[1] * k);
-}
-
-// The cells of one colour of level l that this thread updates (at most
-// two: a level has at most kCoarseCells cells, 2 x 1024 per colour), with
-// the LDS indices of their neighbours and their inverse diagonals, set up
-// once per level and reused by every sweep. A missing neighbour (a
-// non-periodic side) points at a zero slot of the LDS array.
-template <int DIM, typename T>
-struct CSet {
-  int c[2];             // LDS index of the cell, -1 when the slot is empty
-  int nb[2][2 * DIM];   // LDS indices of the neighbours (-d, +d per direction)
-  T idg[2];             // 1 / diagonal
-  int ij[2];            // stretched grid: i | j << 16 of the cell
-};
-
-// beta / h_d^2 of the face between LDS cells ia and ib, from the densities
-// rs in LDS (ib == zero_slot: no face). Evaluated where it is used (the
-// coarse levels are small and their sweeps latency bound), so the cell sets
-// hold no coefficients and stay in registers.
-template <typename T>
-__device__ inline T c_face(const T *rs, int ia, int ib, int zero_slot, T ih2, int d, int met) {
-  return ib == zero_slot ? T(0) : ih2 * face_coef<T>(rs[ia], rs[ib], d, met);
-}
-
-template <int DIM, typename T, bool VC = false, bool MET = false>
-__device__ inline void c_set(const CoarseArgs<T> &a, const T *idg_s, const T *rs, int l, int color, int zero_slot,
-                             CSet<DIM, T> &s, int tid) {
-  const int *n = a.n[l];
-  const int N = (n[0] >> 1) * n[1] * n[2];
-  const int off = a.off[l];
-  const int st[3] = {1, n[0], n[0] * n[1]};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int t = tid + q * blockDim.x;
-    s.c[q] = -1;
-    if (t >= N) continue;
-    int i, j, k;
-    const int c = c_colour_cell<DIM, T>(a, l, color, t, i, j, k);
-    const int qd[3] = {i, j, k};
-    int code = 0;
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      const bool per = a.B.periodic[d] != 0;
-      const bool lo = qd[d] > 0, hi = qd[d] + 1 < n[d];
-      s.nb[q][2 * d] = lo ? off + c - st[d] : (per ? off + c + (n[d] - 1) * st[d] : zero_slot);
-      s.nb[q][2 * d + 1] = hi ? off + c + st[d] : (per ? off + c - (n[d] - 1) * st[d] : zero_slot);
-      code |= ((lo || per) && (hi || per)) ? (1 << d) : 0;
-    }
-    s.c[q] = off + c;
-    if constexpr (MET) {
-      T cf[4];
-      m_faces<T>(rs, a.toff[l], n[0], n[1], i, j, a.ih2[l].v[0], a.ih2[l].v[1], cf);
-      s.idg[q] = T(1) / (((cf[0] + cf[1]) + cf[2]) + cf[3]);
-      s.ij[q] = i | (j << 16);
-    } else if constexpr (VC) {
-      T dg = T(0);
-#pragma unroll
-      for (int m = 0; m < 2 * DIM; ++m)
-        dg += c_face<T>(rs, off + c, s.nb[q][m], zero_slot, a.ih2[l].v[m >> 1], m >> 1, a.met);
-      s.idg[q] = T(1) / dg;
-    } else {
-      s.idg[q] = idg_s[8 * (l - a.l0) + code];
-    }
-  }
-}
-
-// One red/black half-sweep over a cell set: x = (b + sum of neighbours) /
-// diag, all LDS reads of the thread issued before the arithmetic.
-// (A missing neighbour is the zero slot: x = 0 there, so its term vanishes
-// whatever the coefficient.)
-template <int DIM, typename T, bool VC = false, bool MET = false>
-__device__ inline void c_sweep(T *xs, const T *bs, const T *rs, const CSet<DIM, T> &s, const T ih2[3],
-                               bool zero_init, int met, int toff = 0, int n0 = 0, int n1 = 0) {
-  if constexpr (MET) {
-    // stretched 2D grid: coefficients from the level's 1D tables
-    T v[2][4] = {}, bv[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (s.c[q] < 0) continue;
-      if (!zero_init)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) v[q][m] = xs[s.nb[q][m]];
-      bv[q] = bs[s.c[q]];
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (s.c[q] < 0) continue;
-      T cf[4];
-      m_faces<T>(rs, toff, n0, n1, s.ij[q] & 0xffff, s.ij[q] >> 16, ih2[0], ih2[1], cf);
-      T nbs = ((cf[0] * v[q][0] + cf[1] * v[q][1]) + cf[2] * v[q][2]) + cf[3] * v[q][3];
-      if (zero_init) nbs = T(0);
-      xs[s.c[q]] = (bv[q] + nbs) * s.idg[q];
-    }
-    __syncthreads();
-    return;
-  }
-  if constexpr (VC && DIM == 3) {
-    // one cell at a time (fewer live registers); cells of one colour read
-    // only the other colour, so each result is stored at once
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (s.c[q] < 0) continue;
-      const T rc = rs[s.c[q]];
-      T nbs = T(0);
-#pragma unroll
-      for (int m = 0; m < 2 * DIM; ++m) {
-        const int nb = s.nb[q][m];
-        nbs += (ih2[m >> 1] * face_coef<T>(rc, rs[nb], m >> 1, met)) * xs[nb];
-      }
-      if (zero_init) nbs = T(0);
-      xs[s.c[q]] = (bs[s.c[q]] + nbs) * s.idg[q];
-    }
-    __syncthreads();
-    return;
-  }
-  T v[2][2 * DIM] = {}, bv[2], rv[2][VC ? 2 * DIM + 1 : 1];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    if (s.c[q] < 0) continue;
-    if (!zero_init)  // a sweep from zero reads no neighbours
-#pragma unroll
-      for (int m = 0; m < 2 * DIM; ++m) v[q][m] = xs[s.nb[q][m]];
-    bv[q] = bs[s.c[q]];
-    if constexpr (VC) {
-#pragma unroll
-      for (int m = 0; m < 2 * DIM; ++m) rv[q][m] = rs[s.nb[q][m]];
-      rv[q][2 * DIM] = rs[s.c[q]];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    if (s.c[q] < 0) continue;
-    T nbs = T(0);
-    if constexpr (VC) {
-#pragma unroll
-      for (int m = 0; m < 2 * DIM; ++m)
-        nbs += (ih2[m >> 1] * face_coef<T>(rv[q][2 * DIM], rv[q][m], m >> 1, met)) * v[q][m];
-    } else {
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) nbs += ih2[d] * (v[q][2 * d] + v[q][2 * d + 1]);
-    }
-    if (zero_init) nbs = T(0);
-    xs[s.c[q]] = (bv[q] + nbs) * s.idg[q];
-  }
-  __syncthreads();
-}
-
-// The V-cycle over levels l0 .. nlev-1 out of LDS: the right-hand side of
-// level l0 is in bs at off[l0] (the coarser levels' parts are written
-// here), the correction of every level ends in xs, that of level l0 at
-// off[l0]. rs holds the levels' densities (VC), idg_s the inverse
-// diagonals by neighbour code; xs[zero_slot] = 0; tid is threadIdx.x (a
-// caller that runs the cycle in a loop passes it through an opaque copy,
-// so the per-level cell sets are recomputed, not held across iterations).
-// Ends with a barrier.
-template <int DIM, typename T, bool VC, bool MET = false>
-__device__ __attribute__((always_inline)) inline void coarse_cycle(const CoarseArgs<T> &a, T *xs, T *bs, const T *rs,
-                                                                   const T *idg_s, int zero_slot,
-                                                                   int tid) {
-  const int last = a.nlev - 1;
-  for (int l = a.l0; l < last; ++l) {
-    {
-      CSet<DIM, T> red, black;
-      c_set<DIM, T, VC, MET>(a, idg_s, rs, l, 0, zero_slot, red, tid);
-      c_set<DIM, T, VC, MET>(a, idg_s, rs, l, 1, zero_slot, black, tid);
-      for (int s = 0; s < a.nu; ++s) {
-        c_sweep<DIM, T, VC, MET>(xs, bs, rs, red, a.ih2[l].v, s == 0, a.met, a.toff[l], a.n[l][0], a.n[l][1]);
-        c_sweep<DIM, T, VC, MET>(xs, bs, rs, black, a.ih2[l].v, false, a.met, a.toff[l], a.n[l][0], a.n[l][1]);
-      }
-    }
-    const int *nf = a.n[l], *nc = a.n[l + 1];
-    const int Nc = nc[0] * nc[1] * nc[2];
-    const T *x = xs + a.off[l];
-    const T *b = bs + a.off[l];
-
-    // After the last black half-sweep the black cells' residuals vanish
-    // (each was just solved for with its red neighbours final), so only the
-    // red children (dx + dy + dz even) are summed (nu >= 1 always).
-    for (int t = tid; t < Nc; t += blockDim.x) {
-      int I, J, K;
-      c_decode<DIM, T>(nc, t, I, J, K);
-      T acc = T(0);
-      constexpr int kUnroll = VC ? 1 : 2;
-#pragma unroll kUnroll
-      for (int dz = 0; dz < (DIM == 3 ? 2 : 1); ++dz)
-#pragma unroll kUnroll
-        for (int dy = 0; dy < 2; ++dy)
-          for (int dx = (dy + dz) & 1; dx < 2; dx += 2) {
-            const int i = 2 * I + dx, j = 2 * J + dy, k = DIM == 3 ? 2 * K + dz : 0;
-            const int c = i + nf[0] * (j + nf[1] * k);
-            if constexpr (MET) {
-              const int off = a.off[l];
-              const bool pxp = a.B.periodic[0] != 0, pyp = a.B.periodic[1] != 0;
-              const int iw = i > 0 ? off + c - 1 : (pxp ? off + c + nf[0] - 1 : zero_slot);
-              const int ie = i + 1 < nf[0] ? off + c + 1 : (pxp ? off + c - (nf[0] - 1) : zero_slot);
-              const int is = j > 0 ? off + c - nf[0] : (pyp ? off + c + (nf[1] - 1) * nf[0] : zero_slot);
-              const int in = j + 1 < nf[1] ? off + c + nf[0] : (pyp ? off + c - (nf[1] - 1) * nf[0] : zero_slot);
-              T cf[4];
-              m_faces<T>(rs, a.toff[l], nf[0], nf[1], i, j, a.ih2[l].v[0], a.ih2[l].v[1], cf);
-              const T nbs = ((cf[0] * xs[iw] + cf[1] * xs[ie]) + cf[2] * xs[is]) + cf[3] * xs[in];
-              const T dg = ((cf[0] + cf[1]) + cf[2]) + cf[3];
-              acc += b[c] - (dg * x[c] - nbs);
-            } else if constexpr (VC) {
-              // same neighbour rules and coefficients as c_set
-              const int q[3] = {i, j, k};
-              const int st[3] = {1, nf[0], nf[0] * nf[1]};
-              const int off = a.off[l];
-              T nbs = T(0), dg = T(0);
-#pragma unroll
-              for (int d = 0; d < DIM; ++d) {
-                const bool per = a.B.periodic[d] != 0;
-                const bool lo = q[d] > 0, hi = q[d] + 1 < nf[d];
-                const int im = lo ? off + c - st[d] : (per ? off + c + (nf[d] - 1) * st[d] : zero_slot);
-                const int ip = hi ? off + c + st[d] : (per ? off + c - (nf[d] - 1) * st[d] : zero_slot);
-                const T bm = c_face<T>(rs, off + c, im, zero_slot, a.ih2[l].v[d], d, a.met);
-                const T bp = c_face<T>(rs, off + c, ip, zero_slot, a.ih2[l].v[d], d, a.met);
-                nbs += bm * xs[im] + bp * xs[ip];
-                dg += bm + bp;
-              }
-              acc += b[c] - (dg * x[c] - nbs);
-            } else {
-              int code;
-              const T nbs = c_nbs<DIM, T>(nf, a.B, a.ih2[l].v, x, i, j, k, c, code);
-              T dg = T(0);
-#pragma unroll
-              for (int d = 0; d < DIM; ++d) dg += a.ih2[l].v[d] * ((code >> d) & 1 ? T(2) : T(1));
-              acc += b[c] - (dg * x[c] - nbs);
-            }
-          }
-      bs[a.off[l + 1] + t] = acc * (DIM == 3 ? T(0.125) : T(0.25));
-    }
-    __syncthreads();
-  }
-  {
-    // x = pinv b on the coarsest level: 16 lanes per row, each summing a
-    // strided quarter-row share (coalesced: a wavefront reads four row
-    // segments), then a 16-lane xor-shuffle sum; rows beyond the block's
-    // 64 groups of 16 are taken in further rounds.
-    const int *n = a.n[last];
-    const int N = n[0] * n[1] * n[2];
-    const T *bl = bs + a.off[last];
-    const int part = tid & 15, ngroups = blockDim.x >> 4;
-    for (int r = tid >> 4; r - (tid >> 4) < N; r += ngroups) {  // uniform trip count per wavefront
-      T acc = T(0);
-      if (r < N) {
-        const T *row = a.pinv + (long)r * N;
-        for (int col = part; col < N; col += 16) acc += row[col] * bl[col];
-      }
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
-      if (part == 0 && r < N) xs[a.off[last] + r] = acc;
-    }
-    __syncthreads();
-  }
-  for (int l = last - 1; l >= a.l0; --l) {
-    const int *nf = a.n[l], *nc = a.n[l + 1];
-    const int N = nf[0] * nf[1] * nf[2];
-    {
-      // piecewise-constant prolongation to the red cells: the first
-      // post-smoothing half-sweep solves every black cell from its red
-      // neighbours, so the black cells' corrected values would be discarded
-      const int Nr = N >> 1;
-      T xf[2], xc[2];
-      int cf_[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int t = tid + q * blockDim.x;
-        cf_[q] = -1;
-        if (t >= Nr) continue;
-        int i, j, k;
-        const int c = c_colour_cell<DIM, T>(a, l, 0, t, i, j, k);
-        const int pc = (i >> 1) + nc[0] * ((j >> 1) + nc[1] * (DIM == 3 ? (k >> 1) : 0));
-        cf_[q] = a.off[l] + c;
-        xf[q] = xs[cf_[q]];
-        xc[q] = xs[a.off[l + 1] + pc];
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        if (cf_[q] >= 0) xs[cf_[q]] = xf[q] + xc[q];
-    }
-    __syncthreads();
-    CSet<DIM, T> red, black;
-    c_set<DIM, T, VC, MET>(a, idg_s, rs, l, 0, zero_slot, red, tid);
-    c_set<DIM, T, VC, MET>(a, idg_s, rs, l, 1, zero_slot, black, tid);
-    for (int s = 0; s < a.nu; ++s) {
-      c_sweep<DIM, T, VC, MET>(xs, bs, rs, black, a.ih2[l].v, false, a.met, a.toff[l], a.n[l][0], a.n[l][1]);
-      c_sweep<DIM, T, VC, MET>(xs, bs, rs, red, a.ih2[l].v, false, a.met, a.toff[l], a.n[l][0], a.n[l][1]);
-    }
-  }
-}
-
-template <int DIM, typename T, bool VC = false, bool MET = false>
-__global__ void __launch_bounds__(kCoarseThreads) k_mg_coarse(CoarseArgs<T> a, const SolverScalars *sc) {
-  __shared__ T xs[kCoarseLds + 1];     // all coarse levels, then a zero slot
-  __shared__ T bs[kCoarseLds];
-  __shared__ T idg_s[kCoarseLev * 8];  // inverse diagonals, read with a per-cell index
-  __shared__ T rs[VC ? kCoarseLds + 1 : 1];  // densities of all coarse levels (variable coefficients)
-  if (sc->done) return;
-  const int last = a.nlev - 1;
-  const int zero_slot = kCoarseLds;
-  (void)last;
-  if (threadIdx.x < kCoarseLev * 8) idg_s[threadIdx.x] = a.idg[threadIdx.x >> 3][threadIdx.x & 7];
-  if (threadIdx.x == 0) xs[zero_slot] = T(0);
-  if constexpr (MET) {
-    for (int t = threadIdx.x; t < a.mtab_n; t += blockDim.x) rs[t] = a.mtab[t];
-  } else if constexpr (VC) {
-    const int ntot = a.off[last] + a.n[last][0] * a.n[last][1] * a.n[last][2];
-    for (int t = threadIdx.x; t < ntot; t += blockDim.x) rs[t] = a.rho_c[t];
-    if (threadIdx.x == 0) rs[zero_slot] = T(1);
-  }
-  {
-    // all loads of the right-hand side issued before any is used
-    const int *n = a.n[a.l0];
-    const int N = n[0] * n[1] * n[2];
-    T v[kCoarseLoads];
-#pragma unroll
-    for (int q = 0; q < kCoarseLoads; ++q) {
-      const int t = threadIdx.x + q * blockDim.x;
-      v[q] = T(0);
-      if (t < N) {
-        int i, j, k;
-        c_decode<DIM, T>(n, t, i, j, k);
-        const long g = a.L0.at(i, j, k);
-        v[q] = a.b0_double ? (T)((const double *)a.b0)[g] : ((const T *)a.b0)[g];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kCoarseLoads; ++q) {
-      const int t = threadIdx.x + q * blockDim.x;
-      if (t < N) bs[a.off[a.l0] + t] = v[q];
-    }
-    __syncthreads();
-  }
-  coarse_cycle<DIM, T, VC, MET>(a, xs, bs, rs, idg_s, zero_slot, threadIdx.x);
-  {
-    const int *n = a.n[a.l0];
-    const int N = n[0] * n[1] * n[2];
-#pragma unroll
-    for (int q = 0; q < kCoarseLoads; ++q) {
-      const int t = threadIdx.x + q * blockDim.x;
-      if (t >= N) continue;
-      int i, j, k;
-      c_decode<DIM, T>(n, t, i, j, k);
-      a.x0[a.L0.at(i, j, k)] = xs[a.off[a.l0] + t];
     }
   }
 }

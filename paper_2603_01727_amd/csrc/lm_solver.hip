@@ -34,13 +34,13 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "lm_device.h"
 
 namespace lm {
 
-constexpr int kCoarseThreads = 1024;
 constexpr int kRedBlocks = 1024;   // grid of the grid-stride reduction kernels
 // 2D tiles of the fused multigrid kernels: 64 x 16 preferred on the finest
 // level (bandwidth), 32 x 8 below it (latency bound: shorter phases), 16 x 16
@@ -71,16 +71,45 @@ Lay make_layout(int ndim, const int n[3], int elem_bytes) {
 // Small device helpers
 // ---------------------------------------------------------------------------
 
-// Block-wide sums of NV values, identical in every thread: wavefront
-// shuffles, one exchange through LDS, then every thread adds the
-// per-wavefront sums in wavefront order (the tree of block_sum, so the
-// values are bitwise those of block_sum).
+// v plus the value a DPP control moves to this lane (0 where it moves none).
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffLL), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+  return v + __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ inline double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffLL), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+// Sum over the first 16 lanes / the whole wavefront, in every lane: row
+// shifts, then row broadcasts, in the vector unit (a shuffle goes through
+// LDS: six dependent round trips per sum). All lanes active.
+__device__ inline double row_sum16(double v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  return v;  // lane 15 of each row holds the row's sum
+}
+__device__ inline double wave_sum(double v) {
+  v = row_sum16(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return lane_value(v, 63);
+}
+
+// Block-wide sums of NV values (at most 1024 threads, whole wavefronts),
+// identical in every thread: wavefront sums, one exchange through LDS, then
+// every wavefront adds the per-wavefront sums in the same order.
 template <int NV>
 __device__ inline void block_allsum_n(double (&v)[NV]) {
   __shared__ double shn[NV][16];
 #pragma unroll
-  for (int q = 0; q < NV; ++q)
-    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_down(v[q], o, 64);
+  for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
   const int t = linear_tid();
   const int nw = (blockDim.x * blockDim.y * blockDim.z + 63) / 64;
   __syncthreads();  // an earlier call may still be reading shn
@@ -89,11 +118,17 @@ __device__ inline void block_allsum_n(double (&v)[NV]) {
     for (int q = 0; q < NV; ++q) shn[q][t >> 6] = v[q];
   }
   __syncthreads();
+  if (nw <= 4) {
 #pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    double s = 0.0;
-    for (int w = 0; w < nw; ++w) s += shn[q][w];
-    v[q] = s;
+    for (int q = 0; q < NV; ++q) {
+      double s = 0.0;
+      for (int w = 0; w < nw; ++w) s += shn[q][w];
+      v[q] = s;
+    }
+  } else {
+    const int lane = t & 15;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = lane_value(row_sum16(lane < nw ? shn[q][lane] : 0.0), 15);
   }
 }
 
@@ -680,19 +715,11 @@ __global__ void __launch_bounds__(kBlock) k_vc_coef2d(Lay L, Bnd B, T ihx, T ihy
   ig[c] = T(1) / (ihx * (bw + be) + ihy * (bs + bn));
 }
 
-// Density of a coarse-kernel level packed x fastest (the kernel's LDS order).
-template <int DIM, typename T>
-__global__ void __launch_bounds__(kBlock) k_vc_pack(Lay L, const T *r, T *out) {
-  CellPos p;
-  if (!cell_of_thread(L, p)) return;
-  out[p.i + (long)L.n[0] * (p.j + (long)L.n[1] * p.k)] = r[p.c];
-}
-
 }  // namespace lm
 
 #include "lm_mg_kernels.h"
 #include "lm_mg3d.h"
-#include "lm_pcg_block.h"
+#include "lm_coarse.h"
 
 namespace lm {
 
@@ -703,31 +730,31 @@ namespace lm {
 // UNIT: beta = 1 on every face (no densities read).
 constexpr int kPinvThreads = 256;
 template <int DIM, typename T, bool UNIT = false>
-__global__ void __launch_bounds__(kPinvThreads) k_vc_pinv(CoarseArgs<T> a, T *pinv) {
+__global__ void __launch_bounds__(kPinvThreads) k_vc_pinv(Lay L, Bnd B, Ih2<double> ih2v, int met, const T *rho,
+                                                          T *pinv) {
   __shared__ double M[kVcCoarsest * kVcCoarsest];
   __shared__ double rk[kVcCoarsest], ck[kVcCoarsest];
-  const int last = a.nlev - 1;
-  const int *n = a.n[last];
+  const int *n = L.n;
   const int N = n[0] * n[1] * n[2];
-  const T *rho = UNIT ? nullptr : a.rho_c + a.off[last];
   const int t = threadIdx.x;
   const double jn = 1.0 / (double)N;
   for (int e = t; e < N * N; e += blockDim.x) M[e] = jn;
   __syncthreads();
   if (t < N) {
     int i, j, k;
-    c_decode<DIM, T>(n, t, i, j, k);
+    c_decode<DIM>(n, t, i, j, k);
     const int q[3] = {i, j, k};
     const int st[3] = {1, n[0], n[0] * n[1]};
-    const double rc = UNIT ? 1.0 : (double)rho[t];
+    const long g = L.at(i, j, k);
+    const double rc = UNIT ? 1.0 : (double)rho[g];
     for (int d = 0; d < DIM; ++d) {
-      const bool per = a.B.periodic[d] != 0;
-      const double ih2 = (double)a.ih2[last].v[d];
+      const bool per = B.periodic[d] != 0;
+      const double ih2 = (double)(T)ih2v.v[d];
       for (int side = 0; side < 2; ++side) {
         const bool in = side == 0 ? q[d] > 0 : q[d] + 1 < n[d];
         if (!in && !per) continue;
         const int m = side == 0 ? (in ? t - st[d] : t + (n[d] - 1) * st[d]) : (in ? t + st[d] : t - (n[d] - 1) * st[d]);
-        const double w = UNIT ? ih2 : ih2 * face_coef<double>(rc, (double)rho[m], d, a.met);
+        const double w = UNIT ? ih2 : ih2 * face_coef<double>(rc, (double)rho[nbr(L, B, g, q[d], d, side ? 1 : -1)], d, met);
         M[t * N + t] += w;
         M[t * N + m] -= w;
       }
@@ -767,7 +794,6 @@ __global__ void __launch_bounds__(kPinvThreads) k_vc_pinv(CoarseArgs<T> a, T *pi
   for (int e = t; e < N * N; e += blockDim.x) pinv[e] = (T)(M[e] - jn);
 }
 
-static_assert(kCoarseCells <= (long)kCoarseLoads * kCoarseThreads, "coarse loads per thread");
 static_assert(kVcCoarsest <= kPinvThreads, "one thread per coarsest cell");
 }  // namespace lm
 
@@ -851,6 +877,16 @@ static long blocks3d_w(const PoissonWS &ws) { return blocks3d(ws.lev[0].lay, ti3
 
 static bool fused_level(const PoissonWS &ws, int l) { return tile_x(ws, l) > 0; }
 
+// Offset of level l's coefficient sets in those of the coarse-kernel levels
+// (every level but the last is even in all directions: 2^DIM-cell blocks).
+static long coarse_coef_offset(const PoissonWS &ws, int l) {
+  const bool three = ws.lay.ndim == 3;
+  long off = 0;
+  for (int q = ws.lc; q < l && q < ws.nlev - 1; ++q)
+    off += (three ? kBlkSlots<3> * (ws.lev[q].lay.ncells() / 8) : kBlkSlots<2> * (ws.lev[q].lay.ncells() / 4));
+  return off;
+}
+
 bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, const double h[3], int mixed, int flexible,
                   int nu, int vc_cap, std::string *err) {
   ws.lay = fine;
@@ -916,9 +952,7 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
   {
     const char *env = std::getenv("LM_BLOCK_PCG");
     const bool off = env && env[0] == '0';
-    ws.block_pcg = !off && ws.cgcg && ws.lc == 0 && fine.ncells() <= (long)kCoarseLoads * kCoarseThreads;
-    // its scratch: 2 ndim + 1 coefficient vectors, p, s, w and r (compact cell order)
-    ws.blk = ws.block_pcg ? (double *)cv.take((size_t)(2 * fine.ndim + 5) * fine.ncells() * 8) : nullptr;
+    ws.block_pcg = !off && ws.cgcg && ws.lc == 0 && fine.ncells() <= kCoarseCells;
   }
   ws.w = (double *)cv.take(fbytes);
   ws.s[0] = (double *)cv.take(fbytes);
@@ -936,14 +970,17 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
     ws.lev[l].b = cv.take(lb);
   }
   ws.pinv = cv.take((size_t)ncoarsest * ncoarsest * eb);
+  ws.geo = cv.take((size_t)kBlkGeo * sizeof(BlkGeo));
   ws.rho64 = nullptr;
-  ws.rho_c = ws.pinv_vc = nullptr;
+  ws.ccf = ws.pinv_vc = nullptr;
+  ws.ccd = nullptr;
   for (int l = 0; l < kMaxLev; ++l) ws.rho[l] = nullptr;
   if (vc_cap) {
     ws.rho64 = (double *)cv.take(fbytes);
     ws.rho[0] = mixed ? cv.take((size_t)fine.total * eb) : (void *)ws.rho64;
     for (int l = 1; l < nl; ++l) ws.rho[l] = cv.take((size_t)ws.lev[l].lay.total * eb);
-    ws.rho_c = cv.take((size_t)(kCoarseLds + 1) * eb);
+    ws.ccf = cv.take((size_t)coarse_coef_offset(ws, nl - 1) * eb);
+    if (ws.block_pcg && mixed) ws.ccd = (double *)cv.take((size_t)coarse_coef_offset(ws, 1) * 8);
     ws.pinv_vc = cv.take((size_t)ncoarsest * ncoarsest * eb);
   }
   for (int l = 0; l < kMaxLev; ++l)
@@ -970,87 +1007,13 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
   ws.sc = (SolverScalars *)cv.take(sizeof(SolverScalars));
   ws.vol = nullptr;
   ws.met_w = nullptr;
-  ws.met_tab = nullptr;
   if (ws.met) {
-    long nw = 0, nt = 0;
+    long nw = 0;
     for (int l = 0; l < nl; ++l) nw += ws.lev[l].lay.n[0] + ws.lev[l].lay.n[1];
-    for (int l = ws.lc; l < nl; ++l) nt += 2 * (ws.lev[l].lay.n[0] + ws.lev[l].lay.n[1]);
-    if (nt > kCoarseLds) {
-      if (err) *err = "stretched grid: the coarse levels' spacing tables exceed the one-block kernel's LDS";
-      return false;
-    }
     ws.vol = (double *)cv.take(fbytes);
     ws.met_w = (double *)cv.take((size_t)nw * 8);
-    ws.met_tab = cv.take((size_t)nt * eb);
   }
   return true;
-}
-
-// Pseudo-inverse of the coarsest operator: (L + J/N)^{-1} - J/N, where J is
-// the all-ones matrix (L is singular with the constants as null space).
-hipError_t poisson_setup(hipStream_t st, PoissonWS &ws, const double h0[3]) {
-  (void)h0;
-  const MGLevel &m = ws.lev[ws.nlev - 1];
-  const Lay &L = m.lay;
-  const long N = L.ncells();
-  std::vector<double> A((size_t)N * N, 0.0), I((size_t)N * N, 0.0);
-  auto idx = [&](int i, int j, int k) { return (long)i + (long)L.n[0] * (j + (long)L.n[1] * k); };
-  for (int k = 0; k < L.n[2]; ++k)
-    for (int j = 0; j < L.n[1]; ++j)
-      for (int i = 0; i < L.n[0]; ++i) {
-        const long r = idx(i, j, k);
-        const int q[3] = {i, j, k};
-        for (int d = 0; d < L.ndim; ++d) {
-          for (int dir = -1; dir <= 1; dir += 2) {
-            int qq[3] = {q[0], q[1], q[2]};
-            qq[d] += dir;
-            if (qq[d] < 0 || qq[d] >= L.n[d]) {
-              if (!ws.bnd.periodic[d]) continue;
-              qq[d] = (qq[d] + L.n[d]) % L.n[d];
-            }
-            const long cidx = idx(qq[0], qq[1], qq[2]);
-            A[r * N + r] += m.ih2[d];
-            A[r * N + cidx] -= m.ih2[d];
-          }
-        }
-      }
-  for (long a = 0; a < N * N; ++a) A[a] += 1.0 / (double)N;
-  for (long a = 0; a < N; ++a) I[a * N + a] = 1.0;
-  for (long col = 0; col < N; ++col) {  // Gauss-Jordan, partial pivoting
-    long piv = col;
-    for (long r = col + 1; r < N; ++r)
-      if (std::fabs(A[r * N + col]) > std::fabs(A[piv * N + col])) piv = r;
-    if (piv != col)
-      for (long c = 0; c < N; ++c) {
-        std::swap(A[col * N + c], A[piv * N + c]);
-        std::swap(I[col * N + c], I[piv * N + c]);
-      }
-    const double d = A[col * N + col];
-    for (long c = 0; c < N; ++c) {
-      A[col * N + c] /= d;
-      I[col * N + c] /= d;
-    }
-    for (long r = 0; r < N; ++r) {
-      if (r == col) continue;
-      const double f = A[r * N + col];
-      if (f == 0.0) continue;
-      for (long c = 0; c < N; ++c) {
-        A[r * N + c] -= f * A[col * N + c];
-        I[r * N + c] -= f * I[col * N + c];
-      }
-    }
-  }
-  for (long a = 0; a < N * N; ++a) I[a] -= 1.0 / (double)N;
-  hipError_t e;
-  if (ws.mixed) {
-    std::vector<float> f(I.begin(), I.end());
-    e = hipMemcpyAsync(ws.pinv, f.data(), f.size() * 4, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-  } else {
-    e = hipMemcpyAsync(ws.pinv, I.data(), I.size() * 8, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-  }
-  return e;
 }
 
 template <typename T>
@@ -1293,48 +1256,181 @@ static Up2DArgs<T> up_args(PoissonWS &ws, int l, const T *xpre, const T *xc, con
 template <typename T>
 static CoarseArgs<T> coarse_args(PoissonWS &ws, void *z, const double *r) {
   CoarseArgs<T> ca;
-  ca.l0 = ws.lc;
-  ca.nlev = ws.nlev;
+  memset((void *)&ca, 0, sizeof(ca));
+  const int nd = ws.lay.ndim, lc = ws.lc;
+  ca.nq = ws.nlev - lc;
   ca.nu = ws.nu;
-  ca.B = ws.bnd;
-  int off = 0;
-  auto lg2 = [](int v) {
-    int q = 0;
-    while ((1 << q) < v) ++q;
-    return (1 << q) == v ? q : -1;
-  };
-  for (int l = 0; l < ws.nlev; ++l) {
-    for (int d = 0; d < 3; ++d) ca.n[l][d] = ws.lev[l].lay.n[d];
-    ca.lg[l][0] = lg2(ws.lev[l].lay.n[0] / 2);
-    ca.lg[l][1] = lg2(ws.lev[l].lay.n[1]);
-    ca.ih2[l] = ih2_of<T>(ws, l);
-    ca.off[l] = l >= ws.lc ? off : 0;
-    if (l >= ws.lc) off += (int)ws.lev[l].lay.ncells();
-  }
-  for (int q = 0; q < kCoarseLev; ++q) {
-    const int l = ws.lc + q;
+  for (int d = 0; d < 3; ++d) ca.per[d] = ws.bnd.periodic[d];
+  ca.walls = !ws.bnd.all_periodic;
+  int xo = 0, bo = 0;
+  for (int q = 0; q < ca.nq; ++q) {
+    const MGLevel &m = ws.lev[lc + q];
+    BlkLevel<T> &L = ca.lev[q];
+    const bool last = q + 1 == ca.nq;
+    for (int d = 0; d < 3; ++d) {
+      ca.nb[q][d] = last ? 0 : (d < nd ? m.lay.n[d] / 2 : 1);
+      L.ih2[d] = (T)m.ih2[d];
+    }
+    L.nblk = ca.nb[q][0] * ca.nb[q][1] * ca.nb[q][2];
+    L.xo = xo;
+    L.bo = bo;
+    L.go = ca.ngeo;
+    L.co = (int)coarse_coef_offset(ws, lc + q);
+    xo += last ? (int)m.lay.ncells() : (L.nblk + 1) << nd;
+    if (q > 0) bo += last ? (int)m.lay.ncells() : (L.nblk + 1) << nd;
+    ca.ngeo += L.nblk;
+    L.xn = xo;
+    L.bn = bo;
     for (int code = 0; code < 8; ++code) {
       double dg = 0.0;
-      if (l < ws.nlev)
-        for (int d = 0; d < ws.lay.ndim; ++d) dg += ws.lev[l].ih2[d] * (((code >> d) & 1) ? 2.0 : 1.0);
-      ca.idg[q][code] = dg > 0.0 ? (T)(1.0 / dg) : T(0);
+      for (int d = 0; d < nd; ++d) dg += m.ih2[d] * (((code >> d) & 1) ? 2.0 : 1.0);
+      ca.idg[q][code] = (T)(1.0 / dg);
+    }
+    L.idg = ca.idg[q][7];
+    L.dg = (T)(2.0 * (m.ih2[0] + m.ih2[1] + (nd == 3 ? m.ih2[2] : 0.0)));
+  }
+  const Lay &Ll = ws.lev[ws.nlev - 1].lay;
+  for (int d = 0; d < 3; ++d) ca.n_last[d] = Ll.n[d];
+  ca.N_last = (int)Ll.ncells();
+  ca.wave_q = ca.nq;
+  if (ca.N_last <= kBlkPinv)  // then at least the level above the last has at most 64 blocks
+    for (int q = ca.nq - 2; q >= 0 && ca.lev[q].nblk <= 64; --q) ca.wave_q = q;
+  ca.L0 = ws.lev[lc].lay;
+  ca.b0 = lc == 0 ? (const void *)r : ws.lev[lc].b;
+  ca.b0_double = (lc == 0);
+  ca.x0 = lc == 0 ? (T *)z : (T *)ws.lev[lc].x;
+  ca.pinv = (const T *)(ws.vc ? ws.pinv_vc : ws.pinv);
+  ca.cf = ws.vc ? (const T *)ws.ccf : nullptr;
+  ca.geo = (BlkGeo *)ws.geo;
+  return ca;
+}
+
+static hipError_t launch_geo(hipStream_t st, PoissonWS &ws) {
+  const CoarseArgs<double> ca = coarse_args<double>(ws, nullptr, nullptr);
+  if (ca.nq > 1) {
+    const dim3 g(ceil_div(ca.lev[0].nblk, kBlock), ca.nq - 1);
+    if (ws.lay.ndim == 3)
+      hipLaunchKernelGGL((k_blk_geo<3, double>), g, dim3(kBlock), 0, st, ca);
+    else
+      hipLaunchKernelGGL((k_blk_geo<2, double>), g, dim3(kBlock), 0, st, ca);
+  }
+  return hipGetLastError();
+}
+
+// Pseudo-inverse of the coarsest operator: (L + J/N)^{-1} - J/N, where J is
+// the all-ones matrix (L is singular with the constants as null space).
+hipError_t poisson_setup(hipStream_t st, PoissonWS &ws, const double h0[3]) {
+  (void)h0;
+  const MGLevel &m = ws.lev[ws.nlev - 1];
+  const Lay &L = m.lay;
+  const long N = L.ncells();
+  std::vector<double> A((size_t)N * N, 0.0), I((size_t)N * N, 0.0);
+  auto idx = [&](int i, int j, int k) { return (long)i + (long)L.n[0] * (j + (long)L.n[1] * k); };
+  for (int k = 0; k < L.n[2]; ++k)
+    for (int j = 0; j < L.n[1]; ++j)
+      for (int i = 0; i < L.n[0]; ++i) {
+        const long r = idx(i, j, k);
+        const int q[3] = {i, j, k};
+        for (int d = 0; d < L.ndim; ++d) {
+          for (int dir = -1; dir <= 1; dir += 2) {
+            int qq[3] = {q[0], q[1], q[2]};
+            qq[d] += dir;
+            if (qq[d] < 0 || qq[d] >= L.n[d]) {
+              if (!ws.bnd.periodic[d]) continue;
+              qq[d] = (qq[d] + L.n[d]) % L.n[d];
+            }
+            const long cidx = idx(qq[0], qq[1], qq[2]);
+            A[r * N + r] += m.ih2[d];
+            A[r * N + cidx] -= m.ih2[d];
+          }
+        }
+      }
+  for (long a = 0; a < N * N; ++a) A[a] += 1.0 / (double)N;
+  for (long a = 0; a < N; ++a) I[a * N + a] = 1.0;
+  for (long col = 0; col < N; ++col) {  // Gauss-Jordan, partial pivoting
+    long piv = col;
+    for (long r = col + 1; r < N; ++r)
+      if (std::fabs(A[r * N + col]) > std::fabs(A[piv * N + col])) piv = r;
+    if (piv != col)
+      for (long c = 0; c < N; ++c) {
+        std::swap(A[col * N + c], A[piv * N + c]);
+        std::swap(I[col * N + c], I[piv * N + c]);
+      }
+    const double d = A[col * N + col];
+    for (long c = 0; c < N; ++c) {
+      A[col * N + c] /= d;
+      I[col * N + c] /= d;
+    }
+    for (long r = 0; r < N; ++r) {
+      if (r == col) continue;
+      const double f = A[r * N + col];
+      if (f == 0.0) continue;
+      for (long c = 0; c < N; ++c) {
+        A[r * N + c] -= f * A[col * N + c];
+        I[r * N + c] -= f * I[col * N + c];
+      }
     }
   }
-  ca.L0 = ws.lev[ws.lc].lay;
-  ca.b0 = ws.lc == 0 ? (const void *)r : ws.lev[ws.lc].b;
-  ca.b0_double = (ws.lc == 0);
-  ca.x0 = ws.lc == 0 ? (T *)z : (T *)ws.lev[ws.lc].x;
-  ca.pinv = (const T *)(ws.vc ? ws.pinv_vc : ws.pinv);
-  ca.rho_c = ws.vc ? (const T *)ws.rho_c : nullptr;
-  ca.met = ws.met;
-  int toff = 0;
-  for (int l = 0; l < kMaxLev; ++l) {
-    ca.toff[l] = toff;
-    if (ws.met && l >= ws.lc && l < ws.nlev) toff += 2 * (ws.lev[l].lay.n[0] + ws.lev[l].lay.n[1]);
+  for (long a = 0; a < N * N; ++a) I[a] -= 1.0 / (double)N;
+  hipError_t e = launch_geo(st, ws);
+  if (e != hipSuccess) return e;
+  if (ws.mixed) {
+    std::vector<float> f(I.begin(), I.end());
+    e = hipMemcpyAsync(ws.pinv, f.data(), f.size() * 4, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+  } else {
+    e = hipMemcpyAsync(ws.pinv, I.data(), I.size() * 8, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
   }
-  ca.mtab = ws.met ? (const T *)ws.met_tab : nullptr;
-  ca.mtab_n = ws.met ? toff : 0;
-  return ca;
+  return e;
+}
+
+template <int DIM, typename T>
+static void launch_coarse(hipStream_t st, PoissonWS &ws, void *z, const double *r) {
+  const dim3 g(1), b(kBlkThreads<DIM>);
+  if (ws.vc)
+    hipLaunchKernelGGL((k_mg_coarse<DIM, T, true>), g, b, 0, st, coarse_args<T>(ws, z, r), (const SolverScalars *)ws.sc);
+  else
+    hipLaunchKernelGGL((k_mg_coarse<DIM, T, false>), g, b, 0, st, coarse_args<T>(ws, z, r), (const SolverScalars *)ws.sc);
+}
+
+// Coefficient sets of the coarse-kernel levels lc .. lc + nq - 1 from the
+// densities (or cell ratios) of the levels, into out.
+template <int DIM, typename R>
+static void launch_blk_coef(hipStream_t st, PoissonWS &ws, int nq, const R *const rho[], R *out) {
+  BlkCoefArgs<R> a;
+  memset((void *)&a, 0, sizeof(a));
+  a.nq = nq;
+  a.B = ws.bnd;
+  a.met = ws.met;
+  long most = 0;
+  for (int q = 0; q < nq; ++q) {
+    const MGLevel &m = ws.lev[ws.lc + q];
+    a.L[q] = m.lay;
+    a.rho[q] = rho[q];
+    for (int d = 0; d < 3; ++d) a.ih2[q][d] = m.ih2[d];
+    a.co[q] = (int)coarse_coef_offset(ws, ws.lc + q);
+    most = std::max(most, m.lay.ncells() >> DIM);
+  }
+  if (nq > 0)
+    hipLaunchKernelGGL((k_blk_coef<DIM, R>), dim3(ceil_div(most, kBlock), nq), dim3(kBlock), 0, st, a, out);
+}
+
+// Face coefficients and coarsest pseudo-inverse of the variable-coefficient
+// cycle, from the levels' densities (or cell ratios).
+template <int DIM, typename T>
+static void launch_coarse_setup(hipStream_t st, PoissonWS &ws) {
+  const T *rho[kCoarseLev];
+  const int nq = ws.nlev - 1 - ws.lc;
+  for (int q = 0; q < nq; ++q) rho[q] = (const T *)ws.rho[ws.lc + q];
+  launch_blk_coef<DIM, T>(st, ws, nq, rho, (T *)ws.ccf);
+  if (ws.ccd && nq > 0) {
+    const double *r64[1] = {ws.rho64};
+    launch_blk_coef<DIM, double>(st, ws, 1, r64, ws.ccd);
+  }
+  const MGLevel &m = ws.lev[ws.nlev - 1];
+  hipLaunchKernelGGL((k_vc_pinv<DIM, T>), dim3(1), dim3(kPinvThreads), 0, st, m.lay, ws.bnd, ih2_of<double>(ws, ws.nlev - 1),
+                     ws.met, (const T *)ws.rho[ws.nlev - 1], (T *)ws.pinv_vc);
 }
 
 // In-step timing: events for this launch when it is the next timed launch
@@ -1396,13 +1492,7 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg) {
                            (const T *)ws.lev[l].b, (T *)ws.lev[l + 1].b, sc, rl, ws.met);
     }
   }
-  if (DIM == 2 && ws.met)
-    hipLaunchKernelGGL((k_mg_coarse<DIM, T, true, DIM == 2>), dim3(1), dim3(kCoarseThreads), 0, st,
-                       coarse_args<T>(ws, z, r), sc);
-  else if (ws.vc)
-    hipLaunchKernelGGL((k_mg_coarse<DIM, T, true>), dim3(1), dim3(kCoarseThreads), 0, st, coarse_args<T>(ws, z, r), sc);
-  else
-    hipLaunchKernelGGL((k_mg_coarse<DIM, T>), dim3(1), dim3(kCoarseThreads), 0, st, coarse_args<T>(ws, z, r), sc);
+  launch_coarse<DIM, T>(st, ws, z, r);
   for (int l = ws.lc - 1; l >= 0; --l) {
     const Lay &L = ws.lev[l].lay, &Lc = ws.lev[l + 1].lay;
     T *xin = lev_xin<T>(ws, l, z);
@@ -1513,9 +1603,11 @@ static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec,
   pa.L = ws.lay;
   pa.B = ws.bnd;
   for (int d = 0; d < 3; ++d) {
+    pa.n[d] = ws.lay.n[d];
     pa.ih2[d] = ws.lev[0].ih2[d];
     pa.ih[d] = std::sqrt(ws.lev[0].ih2[d]);
   }
+  pa.dg = 2.0 * (pa.ih2[0] + pa.ih2[1] + (DIM == 3 ? pa.ih2[2] : 0.0));
   pa.b = bvec;
   pa.x0 = x0;
   pa.x = ws.x;
@@ -1525,16 +1617,14 @@ static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec,
   pa.mean_w = ws.met ? ws.volume : (double)ws.lay.ncells();
   pa.tol2 = rtol * rtol;
   pa.maxit = maxit;
-  pa.cf = ws.blk;
+  pa.cd = ws.ccd;
   pa.sc = ws.sc;
   pa.log = log;
   ws.tol2 = pa.tol2;
-  if (DIM == 2 && ws.met)
-    hipLaunchKernelGGL((k_pcg_block<DIM, T, true, DIM == 2>), dim3(1), dim3(kCoarseThreads), 0, st, pa);
-  else if (ws.vc)
-    hipLaunchKernelGGL((k_pcg_block<DIM, T, true>), dim3(1), dim3(kCoarseThreads), 0, st, pa);
-  else
-    hipLaunchKernelGGL((k_pcg_block<DIM, T, false>), dim3(1), dim3(kCoarseThreads), 0, st, pa);
+  const bool plain = pa.ca.nq == 1;
+  auto k = ws.vc ? (plain ? &k_pcg_block<DIM, T, true, true> : &k_pcg_block<DIM, T, true, false>)
+                 : (plain ? &k_pcg_block<DIM, T, false, true> : &k_pcg_block<DIM, T, false, false>);
+  hipLaunchKernelGGL(k, dim3(1), dim3(kBlkThreads<DIM>), 0, st, pa);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || log) return e;
   e = hipMemcpyAsync(ws.host_sc, ws.sc, sizeof(SolverScalars), hipMemcpyDeviceToHost, st);
@@ -1650,14 +1740,7 @@ static hipError_t set_beta_dim(hipStream_t st, PoissonWS &ws) {
         hipLaunchKernelGGL((k_vc_coef2d<T>), grid_for(ws.lev[l].lay), bb, 0, st, ws.lev[l].lay, ws.bnd,
                            (T)ws.lev[l].ih2[0], (T)ws.lev[l].ih2[1], (const T *)ws.rho[l], (T *)ws.cf[l][0],
                            (T *)ws.cf[l][1], (T *)ws.cf[l][2]);
-  const int vc = ws.vc;
-  ws.vc = 1;
-  CoarseArgs<T> ca = coarse_args<T>(ws, ws.z[0], ws.r[0]);
-  ws.vc = vc;
-  for (int l = ws.lc; l < ws.nlev; ++l)
-    hipLaunchKernelGGL((k_vc_pack<DIM, T>), grid_for(ws.lev[l].lay), bb, 0, st, ws.lev[l].lay,
-                       (const T *)ws.rho[l], (T *)ws.rho_c + ca.off[l]);
-  hipLaunchKernelGGL((k_vc_pinv<DIM, T>), dim3(1), dim3(kPinvThreads), 0, st, ca, (T *)ws.pinv_vc);
+  launch_coarse_setup<DIM, T>(st, ws);
   return hipGetLastError();
 }
 
@@ -1690,11 +1773,7 @@ static hipError_t set_metric_t(hipStream_t st, PoissonWS &ws) {
     }
   }
   ws.vc = 1;
-  CoarseArgs<T> ca = coarse_args<T>(ws, ws.z[0], ws.r[0]);
-  for (int l = ws.lc; l < ws.nlev; ++l)
-    hipLaunchKernelGGL((k_vc_pack<2, T>), grid_for(ws.lev[l].lay), bb, 0, st, ws.lev[l].lay, (const T *)ws.rho[l],
-                       (T *)ws.rho_c + ca.off[l]);
-  hipLaunchKernelGGL((k_vc_pinv<2, T>), dim3(1), dim3(kPinvThreads), 0, st, ca, (T *)ws.pinv_vc);
+  launch_coarse_setup<2, T>(st, ws);
   return hipGetLastError();
 }
 
@@ -1720,59 +1799,27 @@ hipError_t poisson_set_metric(hipStream_t st, PoissonWS &ws, const double *wx, c
     cy.swap(ny);
   }
   ws.volume = V;
-  // the coarse kernel's tables: per level l >= lc the widths and the face
-  // factors 2 / (w_a + w_b) (the last face wraps when periodic, else 0)
-  std::vector<double> tab;
-  {
-    size_t off = 0;
-    for (int l = 0; l < ws.nlev; ++l) {
-      const int n0 = ws.lev[l].lay.n[0], n1 = ws.lev[l].lay.n[1];
-      if (l >= ws.lc) {
-        const double *lx = all.data() + off, *ly = lx + n0;
-        auto faces = [&](const double *w, int n, int periodic) {
-          for (int q = 0; q < n; ++q) {
-            if (q + 1 < n)
-              tab.push_back(2.0 / (w[q] + w[q + 1]));
-            else
-              tab.push_back(periodic ? 2.0 / (w[q] + w[0]) : 0.0);
-          }
-        };
-        tab.insert(tab.end(), lx, lx + n0);
-        tab.insert(tab.end(), ly, ly + n1);
-        faces(lx, n0, ws.bnd.periodic[0]);
-        faces(ly, n1, ws.bnd.periodic[1]);
-      }
-      off += n0 + n1;
-    }
-  }
   hipError_t e = hipMemcpyAsync(ws.met_w, all.data(), all.size() * 8, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && ws.mixed) {
-    std::vector<float> tf(tab.begin(), tab.end());
-    e = hipMemcpyAsync(ws.met_tab, tf.data(), tf.size() * 4, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-  } else if (e == hipSuccess) {
-    e = hipMemcpyAsync(ws.met_tab, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-  }
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return e;
   return ws.mixed ? set_metric_t<float>(st, ws) : set_metric_t<double>(st, ws);
 }
 
 hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws) {
   if (ws.lev[ws.nlev - 1].lay.ncells() > kVcCoarsest) return hipErrorInvalidValue;
-  const bool three = ws.lay.ndim == 3;
-  if (ws.mixed) {
-    CoarseArgs<float> ca = coarse_args<float>(ws, ws.z[0], ws.r[0]);
-    if (three)
-      hipLaunchKernelGGL((k_vc_pinv<3, float, true>), dim3(1), dim3(kPinvThreads), 0, st, ca, (float *)ws.pinv);
-    else
-      hipLaunchKernelGGL((k_vc_pinv<2, float, true>), dim3(1), dim3(kPinvThreads), 0, st, ca, (float *)ws.pinv);
+  const hipError_t e = launch_geo(st, ws);
+  if (e != hipSuccess) return e;
+  const MGLevel &m = ws.lev[ws.nlev - 1];
+  const Ih2<double> ih2 = ih2_of<double>(ws, ws.nlev - 1);
+  auto run = [&](auto k, auto *out) {
+    hipLaunchKernelGGL(k, dim3(1), dim3(kPinvThreads), 0, st, m.lay, ws.bnd, ih2, 0, (decltype(out))nullptr, out);
+  };
+  if (ws.lay.ndim == 3) {
+    if (ws.mixed) run(&k_vc_pinv<3, float, true>, (float *)ws.pinv);
+    else run(&k_vc_pinv<3, double, true>, (double *)ws.pinv);
   } else {
-    CoarseArgs<double> ca = coarse_args<double>(ws, ws.z[0], ws.r[0]);
-    if (three)
-      hipLaunchKernelGGL((k_vc_pinv<3, double, true>), dim3(1), dim3(kPinvThreads), 0, st, ca, (double *)ws.pinv);
-    else
-      hipLaunchKernelGGL((k_vc_pinv<2, double, true>), dim3(1), dim3(kPinvThreads), 0, st, ca, (double *)ws.pinv);
+    if (ws.mixed) run(&k_vc_pinv<2, float, true>, (float *)ws.pinv);
+    else run(&k_vc_pinv<2, double, true>, (double *)ws.pinv);
   }
   return hipGetLastError();
 }
@@ -1845,8 +1892,7 @@ static hipError_t bench_launch_dim(hipStream_t st, PoissonWS &ws, int which) {
     }
     case 4: hipLaunchKernelGGL((k_cg_update<DIM>), dim3(kRedBlocks), dim3(kBlock), 0, st, a); break;
     case 5:
-      hipLaunchKernelGGL((k_mg_coarse<DIM, T>), dim3(1), dim3(kCoarseThreads), 0, st,
-                         coarse_args<T>(ws, ws.z[0], ws.r[0]), ws.sc);
+      launch_coarse<DIM, T>(st, ws, ws.z[0], ws.r[0]);
       break;
     default: return hipErrorInvalidValue;
   }
