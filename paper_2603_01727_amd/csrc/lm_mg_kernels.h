@@ -2,9 +2,14 @@
 // blocking (one launch per level and direction of the V-cycle), in the
 // constant-coefficient form (beta = 1) and, with VC, in the
 // variable-coefficient form beta = 1/rho_f (face_beta), whose level operators
-// are rediscretised from the level's density (2^d-cell averages).
+// are rediscretised from the level's density (2^d-cell averages). The last
+// tiles of a row or column may reach beyond the grid: positions past a
+// periodic side are halo copies of the cells they wrap to, positions past
+// another side are absent cells, and neither is written.
 // Included by lm_solver.hip only.
 #pragma once
+
+#include <type_traits>
 
 namespace lm {
 
@@ -58,12 +63,30 @@ struct Up2DArgs {
   double *w;          // single-reduction CG: w = A u written on the finest level
   const T *cfx, *cfy, *cig;  // variable-coefficient kernels: west/south face beta, 1/diagonal
   const double *rho64;  // the finest level's FP64 density (FP32 kernels: w = A u in FP64)
+  int met;              // stretched grid: rho64 holds dx/dy (face_coef)
 };
 
 __device__ inline int wrap_or_out(int g, int n, int periodic) {
   if (g >= 0 && g < n) return g;
   if (!periodic) return -1;
   return g < 0 ? g + n : g - n;
+}
+
+// Index of own cell (gx, gy) of a tile; in = false (and a valid index) for a
+// position of an edge tile beyond the grid (ALL: the tile is whole).
+template <bool ALL>
+__device__ inline long own_cell(const Lay &L, int gx, int gy, bool &in) {
+  in = ALL || (gx < L.n[0] && gy < L.n[1]);
+  return in ? L.at(gx, gy, 0) : L.base;
+}
+// Runs f with a compile-time flag for whole tiles: their stores need no
+// per-cell test (with one, each store group is a branch of its own).
+template <typename F>
+__device__ __attribute__((always_inline)) inline void whole_or_edge(bool whole, F &&f) {
+  if (whole)
+    f(std::true_type());
+  else
+    f(std::false_type());
 }
 
 // True when every frame position is a cell with all four neighbours, so
@@ -213,17 +236,17 @@ __device__ inline A lx_vc(const T *xs, const T *fx, const T *fy, int o, A ihx, A
 // coefficients from the FP64 density in global memory, u from the frame.
 template <typename T, int W>
 __device__ inline double lx_vc64(const T *xs, int o, const double *rho64, const Lay &L, const Bnd &B, int gx, int gy,
-                                 double ihx, double ihy) {
+                                 double ihx, double ihy, int met) {
 #pragma clang fp contract(off)
   const long c = L.at(gx, gy, 0);
   const int nx = L.n[0], ny = L.n[1];
   const long sy = L.s[1];
   const double rc = rho64[c];
   double bw = 0.0, be = 0.0, bs_ = 0.0, bn = 0.0;
-  if (B.periodic[0] || gx > 0) bw = face_beta<double>(rc, rho64[gx > 0 ? c - 1 : c + (nx - 1)]);
-  if (B.periodic[0] || gx + 1 < nx) be = face_beta<double>(rc, rho64[gx + 1 < nx ? c + 1 : c - (nx - 1)]);
-  if (B.periodic[1] || gy > 0) bs_ = face_beta<double>(rc, rho64[gy > 0 ? c - sy : c + (long)(ny - 1) * sy]);
-  if (B.periodic[1] || gy + 1 < ny) bn = face_beta<double>(rc, rho64[gy + 1 < ny ? c + sy : c - (long)(ny - 1) * sy]);
+  if (B.periodic[0] || gx > 0) bw = face_coef<double>(rc, rho64[gx > 0 ? c - 1 : c + (nx - 1)], 0, met);
+  if (B.periodic[0] || gx + 1 < nx) be = face_coef<double>(rc, rho64[gx + 1 < nx ? c + 1 : c - (nx - 1)], 0, met);
+  if (B.periodic[1] || gy > 0) bs_ = face_coef<double>(rc, rho64[gy > 0 ? c - sy : c + (long)(ny - 1) * sy], 1, met);
+  if (B.periodic[1] || gy + 1 < ny) bn = face_coef<double>(rc, rho64[gy + 1 < ny ? c + sy : c - (long)(ny - 1) * sy], 1, met);
   const double dg = ihx * (bw + be) + ihy * (bs_ + bn);
   return dg * (double)xs[o] - (ihx * (bw * (double)xs[o - 1] + be * (double)xs[o + 1]) +
                                ihy * (bs_ * (double)xs[o - W] + bn * (double)xs[o + W]));
@@ -273,6 +296,7 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
   const int p0 = (gx0 + gy0) & 1;
   const int tid = threadIdx.x;
   const bool fast = frame_interior(a.B, gx0, gy0, W, HH, nx, ny);
+  const bool whole = gx0 + H + TXT <= nx && gy0 + H + TYT <= ny;
   double alpha = 0.0, beta = 0.0;
   const bool cg = a.finest && a.k >= 1;
   if (cg && a.cgcg) {
@@ -367,33 +391,38 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
       if (o < NPOS) bs[o] = ok[it] ? (T)(rv[it] - alpha * (wv[it] + beta * sv[it])) : T(0);
     }
     // own cells: p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s
-    constexpr int NOWN = TXT * TYT / kBlock;
-    long oi[NOWN];
-    double ro[NOWN], wo[NOWN], so[NOWN], xo[NOWN], po[NOWN];
-    T uo[NOWN];
+    whole_or_edge(whole, [&](auto Wh) __attribute__((always_inline)) {
+      constexpr bool ALL = decltype(Wh)::value;
+      constexpr int NOWN = TXT * TYT / kBlock;
+      long oi[NOWN];
+      bool in[NOWN];
+      double ro[NOWN], wo[NOWN], so[NOWN], xo[NOWN], po[NOWN];
+      T uo[NOWN];
 #pragma unroll
-    for (int u = 0; u < NOWN; ++u) {
-      const int o = tid + u * kBlock;
-      oi[u] = a.Lf.at(gx0 + H + o % TXT, gy0 + H + o / TXT, 0);
-    }
+      for (int u = 0; u < NOWN; ++u) {
+        const int o = tid + u * kBlock;
+        oi[u] = own_cell<ALL>(a.Lf, gx0 + H + o % TXT, gy0 + H + o / TXT, in[u]);
+      }
 #pragma unroll
-    for (int u = 0; u < NOWN; ++u) {
-      ro[u] = rb[oi[u]];
-      wo[u] = a.w[oi[u]];
-      so[u] = old ? a.s_old[oi[u]] : 0.0;
-      po[u] = old ? a.p_io[oi[u]] : 0.0;
-      xo[u] = a.x[oi[u]];
-      uo[u] = a.u[oi[u]];
-    }
+      for (int u = 0; u < NOWN; ++u) {
+        ro[u] = rb[oi[u]];
+        wo[u] = a.w[oi[u]];
+        so[u] = old ? a.s_old[oi[u]] : 0.0;
+        po[u] = old ? a.p_io[oi[u]] : 0.0;
+        xo[u] = a.x[oi[u]];
+        uo[u] = a.u[oi[u]];
+      }
 #pragma unroll
-    for (int u = 0; u < NOWN; ++u) {
-      const double pn = (double)uo[u] + beta * po[u];
-      const double sn = wo[u] + beta * so[u];
-      a.p_io[oi[u]] = pn;
-      a.s_new[oi[u]] = sn;
-      a.x[oi[u]] = xo[u] + alpha * pn;
-      a.rnew[oi[u]] = ro[u] - alpha * (wo[u] + beta * so[u]);
-    }
+      for (int u = 0; u < NOWN; ++u) {
+        const double pn = (double)uo[u] + beta * po[u];
+        const double sn = wo[u] + beta * so[u];
+        if (!in[u]) continue;
+        a.p_io[oi[u]] = pn;
+        a.s_new[oi[u]] = sn;
+        a.x[oi[u]] = xo[u] + alpha * pn;
+        a.rnew[oi[u]] = ro[u] - alpha * (wo[u] + beta * so[u]);
+      }
+    });
   } else if (a.finest) {
     const double *rb = (const double *)a.b;
     double rv[NIT], qv[NIT];
@@ -408,26 +437,31 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
       if (o < NPOS) bs[o] = ok[it] ? (T)(rv[it] - alpha * qv[it]) : T(0);
     }
     if (cg) {  // CG update of the tile's own cells
-      constexpr int NOWN = TXT * TYT / kBlock;
-      long oi[NOWN];
-      double ro[NOWN], qo[NOWN], xo[NOWN], po[NOWN];
+      whole_or_edge(whole, [&](auto Wh) __attribute__((always_inline)) {
+        constexpr bool ALL = decltype(Wh)::value;
+        constexpr int NOWN = TXT * TYT / kBlock;
+        long oi[NOWN];
+        bool in[NOWN];
+        double ro[NOWN], qo[NOWN], xo[NOWN], po[NOWN];
 #pragma unroll
-      for (int u = 0; u < NOWN; ++u) {
-        const int o = tid + u * kBlock;
-        oi[u] = a.Lf.at(gx0 + H + o % TXT, gy0 + H + o / TXT, 0);
-      }
+        for (int u = 0; u < NOWN; ++u) {
+          const int o = tid + u * kBlock;
+          oi[u] = own_cell<ALL>(a.Lf, gx0 + H + o % TXT, gy0 + H + o / TXT, in[u]);
+        }
 #pragma unroll
-      for (int u = 0; u < NOWN; ++u) {
-        ro[u] = rb[oi[u]];
-        qo[u] = a.q[oi[u]];
-        xo[u] = a.x[oi[u]];
-        po[u] = a.p[oi[u]];
-      }
+        for (int u = 0; u < NOWN; ++u) {
+          ro[u] = rb[oi[u]];
+          qo[u] = a.q[oi[u]];
+          xo[u] = a.x[oi[u]];
+          po[u] = a.p[oi[u]];
+        }
 #pragma unroll
-      for (int u = 0; u < NOWN; ++u) {
-        a.rnew[oi[u]] = ro[u] - alpha * qo[u];
-        a.x[oi[u]] = xo[u] + alpha * po[u];
-      }
+        for (int u = 0; u < NOWN; ++u) {
+          if (!in[u]) continue;
+          a.rnew[oi[u]] = ro[u] - alpha * qo[u];
+          a.x[oi[u]] = xo[u] + alpha * po[u];
+        }
+      });
     }
   } else {
     const T *bb = (const T *)a.b;
@@ -448,12 +482,18 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
   } else {
     sweeps<T, W, HH, 1, 2 * NU, 1>(xs, bs, p0, gx0, gy0, nx, ny, a.B, a.ihx, a.ihy, a.idg, fast, true);
   }
-  for (int o = tid; o < TXT * TYT; o += kBlock) {
-    const int lx = H + o % TXT, ly = H + o / TXT;
-    a.xpre[a.Lf.at(gx0 + lx, gy0 + ly, 0)] = xs[ly * W + lx];
-  }
+  whole_or_edge(whole, [&](auto Wh) __attribute__((always_inline)) {
+    for (int o = tid; o < TXT * TYT; o += kBlock) {
+      const int lx = H + o % TXT, ly = H + o / TXT;
+      bool in;
+      const long c = own_cell<decltype(Wh)::value>(a.Lf, gx0 + lx, gy0 + ly, in);
+      if (in) a.xpre[c] = xs[ly * W + lx];
+    }
+  });
   for (int o = tid; o < (TXT / 2) * (TYT / 2); o += kBlock) {
     const int cx = o % (TXT / 2), cy = o / (TXT / 2);
+    const int Cx = (gx0 + H) / 2 + cx, Cy = (gy0 + H) / 2 + cy;
+    if (Cx >= a.Lc.n[0] || Cy >= a.Lc.n[1]) continue;
     T acc = T(0);
 #pragma unroll
     for (int dy = 0; dy < 2; ++dy)
@@ -470,7 +510,6 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
           Lx = lx_general<T, W>(xs, off, gx0 + lx, gy0 + ly, nx, ny, a.B, a.ihx, a.ihy);
         acc += bs[off] - Lx;
       }
-    const int Cx = (gx0 + H) / 2 + cx, Cy = (gy0 + H) / 2 + cy;
     a.bc[a.Lc.at(Cx, Cy, 0)] = acc * T(0.25);
   }
 }
@@ -495,6 +534,7 @@ __global__ void __launch_bounds__(kBlock) k_mg_up2d(Up2DArgs<T> a) {
   const int p0 = (gx0 + gy0) & 1;
   const int tid = threadIdx.x;
   const bool fast = frame_interior(a.B, gx0, gy0, W, HH, nx, ny);
+  const bool whole = gx0 + H + TXT <= nx && gy0 + H + TYT <= ny;
   constexpr int NPOS = W * HH;
   constexpr int NIT = (NPOS + kBlock - 1) / kBlock;
   long gi[NIT], ci[NIT];
@@ -545,79 +585,84 @@ __global__ void __launch_bounds__(kBlock) k_mg_up2d(Up2DArgs<T> a) {
   } else {
     sweeps<T, W, HH, 1, 2 * NU, 0>(xs, bs, p0, gx0, gy0, nx, ny, a.B, a.ihx, a.ihy, a.idg, fast, false);
   }
-  double rz = 0.0, rr = 0.0, rzo = 0.0;
-  constexpr int NOWN = TXT * TYT / kBlock;
-  long oi[NOWN];
-  T zv[NOWN];
-#pragma unroll
-  for (int u = 0; u < NOWN; ++u) {
-    const int o = tid + u * kBlock;
-    const int lx = H + o % TXT, ly = H + o / TXT;
-    oi[u] = a.Lf.at(gx0 + lx, gy0 + ly, 0);
-    zv[u] = xs[ly * W + lx];
-    a.xout[oi[u]] = zv[u];
-  }
-  if (EXTRA && a.finest) {
-    double rv[NOWN];
-#pragma unroll
-    for (int u = 0; u < NOWN; ++u) rv[u] = ((const double *)a.b)[oi[u]];
-    double ru = 0.0, wu = 0.0;
+  whole_or_edge(whole, [&](auto Wh) __attribute__((always_inline)) {
+    constexpr bool ALL = decltype(Wh)::value;
+    double rz = 0.0, rr = 0.0, rzo = 0.0;
+    constexpr int NOWN = TXT * TYT / kBlock;
+    long oi[NOWN];
+    bool in[NOWN];
+    T zv[NOWN];
 #pragma unroll
     for (int u = 0; u < NOWN; ++u) {
       const int o = tid + u * kBlock;
       const int lx = H + o % TXT, ly = H + o / TXT;
-      const int off = ly * W + lx;
-      double Lu;
-      if constexpr (VC) {
-        if constexpr (sizeof(T) == 8)
-          Lu = lx_vc<T, W, double>(xs, fx, fy, off, a.dihx, a.dihy);
-        else
-          Lu = lx_vc64<T, W>(xs, off, a.rho64, a.Lf, a.B, gx0 + lx, gy0 + ly, a.dihx, a.dihy);
-      } else if (fast) {
-        Lu = (2.0 * (a.dihx + a.dihy)) * (double)xs[off] -
-             (a.dihx * ((double)xs[off - 1] + (double)xs[off + 1]) + a.dihy * ((double)xs[off - W] + (double)xs[off + W]));
-      } else {
-        Lu = lx_general<T, W, double>(xs, off, gx0 + lx, gy0 + ly, nx, ny, a.B, a.dihx, a.dihy);
+      oi[u] = own_cell<ALL>(a.Lf, gx0 + lx, gy0 + ly, in[u]);
+      zv[u] = in[u] ? xs[ly * W + lx] : T(0);
+      if (in[u]) a.xout[oi[u]] = zv[u];
+    }
+    if (EXTRA && a.finest) {
+      double rv[NOWN];
+#pragma unroll
+      for (int u = 0; u < NOWN; ++u) rv[u] = in[u] ? ((const double *)a.b)[oi[u]] : 0.0;
+      double ru = 0.0, wu = 0.0;
+#pragma unroll
+      for (int u = 0; u < NOWN; ++u) {
+        const int o = tid + u * kBlock;
+        const int lx = H + o % TXT, ly = H + o / TXT;
+        const int off = ly * W + lx;
+        if (!in[u]) continue;
+        double Lu;
+        if constexpr (VC) {
+          if constexpr (sizeof(T) == 8)
+            Lu = lx_vc<T, W, double>(xs, fx, fy, off, a.dihx, a.dihy);
+          else
+            Lu = lx_vc64<T, W>(xs, off, a.rho64, a.Lf, a.B, gx0 + lx, gy0 + ly, a.dihx, a.dihy, a.met);
+        } else if (fast) {
+          Lu = (2.0 * (a.dihx + a.dihy)) * (double)xs[off] -
+               (a.dihx * ((double)xs[off - 1] + (double)xs[off + 1]) + a.dihy * ((double)xs[off - W] + (double)xs[off + W]));
+        } else {
+          Lu = lx_general<T, W, double>(xs, off, gx0 + lx, gy0 + ly, nx, ny, a.B, a.dihx, a.dihy);
+        }
+        const double wv = Lu;
+        a.w[oi[u]] = wv;
+        ru += rv[u] * (double)zv[u];
+        wu += wv * (double)zv[u];
+        rr += rv[u] * rv[u];
       }
-      const double wv = Lu;
-      a.w[oi[u]] = wv;
-      ru += rv[u] * (double)zv[u];
-      wu += wv * (double)zv[u];
-      rr += rv[u] * rv[u];
+      double v3[3] = {ru, wu, rr};
+      block_allsum_n<3>(v3);
+      if (linear_tid() == 0) {
+        a.part_rz[blockIdx.x] = v3[0];
+        a.part_rz[a.np + blockIdx.x] = v3[1];
+        a.part_rz[2 * a.np + blockIdx.x] = v3[2];
+      }
+      return;
     }
-    double v3[3] = {ru, wu, rr};
-    block_allsum_n<3>(v3);
-    if (linear_tid() == 0) {
-      a.part_rz[blockIdx.x] = v3[0];
-      a.part_rz[a.np + blockIdx.x] = v3[1];
-      a.part_rz[2 * a.np + blockIdx.x] = v3[2];
-    }
-    return;
-  }
-  if (a.finest) {
-    double rv[NOWN];
-    T zo[NOWN];
+    if (a.finest) {
+      double rv[NOWN];
+      T zo[NOWN];
 #pragma unroll
-    for (int u = 0; u < NOWN; ++u) {
-      rv[u] = ((const double *)a.b)[oi[u]];
-      zo[u] = a.zold ? a.zold[oi[u]] : T(0);
-    }
+      for (int u = 0; u < NOWN; ++u) {
+        rv[u] = in[u] ? ((const double *)a.b)[oi[u]] : 0.0;
+        zo[u] = a.zold && in[u] ? a.zold[oi[u]] : T(0);
+      }
 #pragma unroll
-    for (int u = 0; u < NOWN; ++u) {
-      rz += rv[u] * (double)zv[u];
-      rr += rv[u] * rv[u];
-      rzo += rv[u] * (double)zo[u];
+      for (int u = 0; u < NOWN; ++u) {
+        rz += rv[u] * (double)zv[u];
+        rr += rv[u] * rv[u];
+        rzo += rv[u] * (double)zo[u];
+      }
     }
-  }
-  if (a.finest) {
-    double v3[3] = {rz, rr, rzo};  // rzo stays 0 without z_old
-    block_allsum_n<3>(v3);
-    if (linear_tid() == 0) {
-      a.part_rz[blockIdx.x] = v3[0];
-      a.part_rz[a.np + blockIdx.x] = v3[1];
-      a.part_rz[2 * a.np + blockIdx.x] = v3[2];
+    if (a.finest) {
+      double v3[3] = {rz, rr, rzo};  // rzo stays 0 without z_old
+      block_allsum_n<3>(v3);
+      if (linear_tid() == 0) {
+        a.part_rz[blockIdx.x] = v3[0];
+        a.part_rz[a.np + blockIdx.x] = v3[1];
+        a.part_rz[2 * a.np + blockIdx.x] = v3[2];
+      }
     }
-  }
+  });
 }
 
 }  // namespace lm

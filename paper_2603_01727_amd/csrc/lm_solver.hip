@@ -21,7 +21,7 @@
 // raises a flag that turns every later kernel into an immediate return; the
 // host queues iterations in batches and reads the flag once per batch.
 //
-// Levels. 2D levels whose sizes are multiples of the tile run one LDS tile
+// Levels. 2D levels run one LDS tile
 // kernel per level and direction with temporal blocking (nu red-black sweeps
 // from a zero guess, residual and restriction on the way down; prolongation
 // and nu black-red sweeps on the way up; on the finest level also the CG
@@ -698,7 +698,7 @@ __global__ void __launch_bounds__(kBlock) k_vc_rho_down(Lay Lf, Lay Lc, const TS
 // operations as op_parts_vc, so the same bits).
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_vc_coef2d(Lay L, Bnd B, T ihx, T ihy, const T *rho, T *fx, T *fy,
-                                                      T *ig) {
+                                                      T *ig, int met) {
 #pragma clang fp contract(off)
   CellPos p;
   if (!cell_of_thread(L, p)) return;
@@ -706,10 +706,10 @@ __global__ void __launch_bounds__(kBlock) k_vc_coef2d(Lay L, Bnd B, T ihx, T ihy
   const long c = p.c, sy = L.s[1];
   const T rc = rho[c];
   T bw = T(0), be = T(0), bs = T(0), bn = T(0);
-  if (B.periodic[0] || p.i > 0) bw = face_beta<T>(rc, rho[p.i > 0 ? c - 1 : c + (nx - 1)]);
-  if (B.periodic[0] || p.i + 1 < nx) be = face_beta<T>(rc, rho[p.i + 1 < nx ? c + 1 : c - (nx - 1)]);
-  if (B.periodic[1] || p.j > 0) bs = face_beta<T>(rc, rho[p.j > 0 ? c - sy : c + (long)(ny - 1) * sy]);
-  if (B.periodic[1] || p.j + 1 < ny) bn = face_beta<T>(rc, rho[p.j + 1 < ny ? c + sy : c - (long)(ny - 1) * sy]);
+  if (B.periodic[0] || p.i > 0) bw = face_coef<T>(rc, rho[p.i > 0 ? c - 1 : c + (nx - 1)], 0, met);
+  if (B.periodic[0] || p.i + 1 < nx) be = face_coef<T>(rc, rho[p.i + 1 < nx ? c + 1 : c - (nx - 1)], 0, met);
+  if (B.periodic[1] || p.j > 0) bs = face_coef<T>(rc, rho[p.j > 0 ? c - sy : c + (long)(ny - 1) * sy], 1, met);
+  if (B.periodic[1] || p.j + 1 < ny) bn = face_coef<T>(rc, rho[p.j + 1 < ny ? c + sy : c - (long)(ny - 1) * sy], 1, met);
   fx[c] = bw;
   fy[c] = bs;
   ig[c] = T(1) / (ihx * (bw + be) + ihy * (bs + bn));
@@ -806,34 +806,60 @@ namespace lm {
 static int tile_x(const PoissonWS &ws, int l) { return ws.vc ? ws.vtx[l] : ws.tx[l]; }
 static int tile_y(const PoissonWS &ws, int l) { return ws.vc ? ws.vty[l] : ws.ty[l]; }
 
-// Tile of 2D level l (< lc), or 0 x 0 when no tile divides it.
+// Tiles of a level along each direction / in all (the last ones may reach
+// beyond the grid).
+static int tiles_along(int n, int t) { return (n + t - 1) / t; }
+static int tiles2d(const Lay &L, int tx, int ty) { return tiles_along(L.n[0], tx) * tiles_along(L.n[1], ty); }
+
+// Tile of 2D level l (< lc) among the candidates, or 0 x 0 when none fits:
+// the first that divides the level, else the one with the fewest cells in
+// its frames (the halos included, which is what an edge tile costs: 120 x 88
+// by 16 x 16 is 48 frames of 676 cells against 44 of 756 by 32 x 8). A frame
+// may reach past the far side by less than a period only (wrap_or_out wraps
+// once); smaller levels run the unfused kernels. Measured: a level of 96^2
+// (stretched, FP64) or 120 x 88 (FP32) takes ten unfused launches of 3.3 - 5
+// us per cycle, two tiled ones of 5 us: 8 steps of the 96^2 cavity 14.3 ->
+// 6.4 ms, of 240 x 176 11.5 -> 7.0 ms.
+static void fit_tile(const Lay &L, int nu, const int (*cand)[2], int nc, int &tx, int &ty) {
+  tx = ty = 0;
+  for (int q = 0; q < nc; ++q)
+    if (L.n[0] % cand[q][0] == 0 && L.n[1] % cand[q][1] == 0) {
+      tx = cand[q][0];
+      ty = cand[q][1];
+      return;
+    }
+  const int H = 2 * nu + 1;
+  long best = 0;
+  for (int q = 0; q < nc; ++q) {
+    const int cx = cand[q][0], cy = cand[q][1];
+    if (L.n[0] < cx + H || L.n[1] < cy + H) continue;
+    const long cost = (long)tiles2d(L, cx, cy) * (cx + 2 * H) * (cy + 2 * H);
+    if (tx == 0 || cost < best) {
+      tx = cx;
+      ty = cy;
+      best = cost;
+    }
+  }
+}
+
 static void choose_tile(PoissonWS &ws, int l) {
   const Lay &L = ws.lev[l].lay;
   ws.tx[l] = ws.ty[l] = 0;
-  if (L.ndim != 2 || ws.nu < 1 || ws.nu > 3 || l >= ws.lc) return;
+  if (ws.met || L.ndim != 2 || ws.nu < 1 || ws.nu > 3 || l >= ws.lc) return;
   const int cand[3][2] = {{TX, TY}, {TXS, TYS}, {16, 16}};
-  for (int q = (l == 0 ? 0 : 1); q < 3; ++q)
-    if (L.n[0] % cand[q][0] == 0 && L.n[1] % cand[q][1] == 0) {
-      ws.tx[l] = cand[q][0];
-      ws.ty[l] = cand[q][1];
-      return;
-    }
+  const int q = l == 0 ? 0 : 1;
+  fit_tile(L, ws.nu, cand + q, 3 - q, ws.tx[l], ws.ty[l]);
 }
 
-// Tile of 2D level l (< lc) for the variable-coefficient kernels, whose
-// frames carry three more LDS arrays (face coefficients, 1/diagonal): the
-// small tiles only.
+// Tile of 2D level l (< lc) for the variable-coefficient kernels (stretched
+// grids too), whose frames carry three more LDS arrays (face coefficients,
+// 1/diagonal): the small tiles only.
 static void choose_tile_vc(PoissonWS &ws, int l) {
   const Lay &L = ws.lev[l].lay;
   ws.vtx[l] = ws.vty[l] = 0;
-  if (!ws.vc_cap || ws.met || L.ndim != 2 || ws.nu < 1 || ws.nu > 3 || l >= ws.lc) return;
+  if (!ws.vc_cap || L.ndim != 2 || ws.nu < 1 || ws.nu > 3 || l >= ws.lc) return;
   const int cand[2][2] = {{TXS, TYS}, {16, 16}};
-  for (int q = 0; q < 2; ++q)
-    if (L.n[0] % cand[q][0] == 0 && L.n[1] % cand[q][1] == 0) {
-      ws.vtx[l] = cand[q][0];
-      ws.vty[l] = cand[q][1];
-      return;
-    }
+  fit_tile(L, ws.nu, cand, 2, ws.vtx[l], ws.vty[l]);
 }
 
 // Fused 3D level kernels: the owned tile edge is the 32-cell frame less
@@ -996,8 +1022,8 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
       for (int q = 0; q < 3; ++q) ws.cf[l][q] = cv.take((size_t)ws.lev[l].lay.total * eb);
   }
   long npmax = kRedBlocks;
-  if (ws.tx[0] > 0) npmax = std::max(npmax, (long)(fine.n[0] / ws.tx[0]) * (fine.n[1] / ws.ty[0]) + 1);
-  if (ws.vtx[0] > 0) npmax = std::max(npmax, (long)(fine.n[0] / ws.vtx[0]) * (fine.n[1] / ws.vty[0]) + 1);
+  if (ws.tx[0] > 0) npmax = std::max(npmax, (long)tiles2d(fine, ws.tx[0], ws.ty[0]) + 1);
+  if (ws.vtx[0] > 0) npmax = std::max(npmax, (long)tiles2d(fine, ws.vtx[0], ws.vty[0]) + 1);
   if (fused3d(ws, 0) && blocks3d_w(ws) > npmax) npmax = blocks3d_w(ws);
   ws.np_max = npmax;
   ws.part_cc = (double *)cv.take((size_t)npmax * 8);
@@ -1146,7 +1172,7 @@ template <typename T>
 static void launch_nu(const PoissonWS &ws, int l, int nu, Down2DArgs<T> &a, hipStream_t st, hipEvent_t e0 = nullptr,
                       hipEvent_t e1 = nullptr) {
   const int tx = tile_x(ws, l), ty = tile_y(ws, l);
-  const dim3 g((a.Lf.n[0] / tx) * (a.Lf.n[1] / ty));
+  const dim3 g(tiles2d(a.Lf, tx, ty));
   if (ws.vc) {
     if (tx == TXS && ty == TYS)
       launch_nu_vc<T, TXS, TYS>(nu, a, g, st, e0, e1);
@@ -1164,7 +1190,7 @@ static void launch_nu(const PoissonWS &ws, int l, int nu, Down2DArgs<T> &a, hipS
 template <typename T>
 static void launch_nu(const PoissonWS &ws, int l, int nu, Up2DArgs<T> &a, hipStream_t st, bool extra) {
   const int tx = tile_x(ws, l), ty = tile_y(ws, l);
-  const dim3 g((a.Lf.n[0] / tx) * (a.Lf.n[1] / ty));
+  const dim3 g(tiles2d(a.Lf, tx, ty));
   if (ws.vc) {
     if (tx == TXS && ty == TYS)
       launch_nu_vc<T, TXS, TYS>(nu, a, g, st, extra);
@@ -1203,7 +1229,7 @@ static Down2DArgs<T> down_args(PoissonWS &ws, int l, int k, const void *b, T *xp
   a.part_pq = ws.part_pq;
   a.np_pq = kRedBlocks;
   a.sc = ws.sc;
-  a.tiles_x = L.n[0] / tile_x(ws, l);
+  a.tiles_x = tiles_along(L.n[0], tile_x(ws, l));
   // single-reduction CG (finest level, FP64)
   a.cgcg = ws.cgcg && l == 0;
   a.u = (const T *)ws.z[0];
@@ -1213,7 +1239,7 @@ static Down2DArgs<T> down_args(PoissonWS &ws, int l, int k, const void *b, T *xp
   a.p_io = ws.p[0];
   a.part_g = ws.part_rz;
   a.part_cc = ws.part_cc;
-  a.np_g = fused_level(ws, 0) ? (ws.lay.n[0] / tile_x(ws, 0)) * (ws.lay.n[1] / tile_y(ws, 0)) : 0;
+  a.np_g = fused_level(ws, 0) ? tiles2d(ws.lay, tile_x(ws, 0), tile_y(ws, 0)) : 0;
   a.np_cc = kRedBlocks;
   a.tol2 = ws.tol2;
   a.cfx = ws.vc ? (const T *)ws.cf[l][0] : nullptr;
@@ -1242,14 +1268,15 @@ static Up2DArgs<T> up_args(PoissonWS &ws, int l, const T *xpre, const T *xc, con
   a.finest = (l == 0);
   a.zold = zold;
   a.part_rz = ws.part_rz;
-  a.np = (L.n[0] / tile_x(ws, l)) * (L.n[1] / tile_y(ws, l));
+  a.np = tiles2d(L, tile_x(ws, l), tile_y(ws, l));
   a.sc = ws.sc;
-  a.tiles_x = L.n[0] / tile_x(ws, l);
+  a.tiles_x = tiles_along(L.n[0], tile_x(ws, l));
   a.w = ws.w;
   a.cfx = ws.vc ? (const T *)ws.cf[l][0] : nullptr;
   a.cfy = ws.vc ? (const T *)ws.cf[l][1] : nullptr;
   a.cig = ws.vc ? (const T *)ws.cf[l][2] : nullptr;
   a.rho64 = ws.vc ? ws.rho64 : nullptr;
+  a.met = ws.met;
   return a;
 }
 
@@ -1546,7 +1573,7 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg) {
 }
 
 static int np_rz_of(const PoissonWS &ws) {
-  if (fused_level(ws, 0)) return (ws.lay.n[0] / tile_x(ws, 0)) * (ws.lay.n[1] / tile_y(ws, 0));
+  if (fused_level(ws, 0)) return tiles2d(ws.lay, tile_x(ws, 0), tile_y(ws, 0));
   if (w_in_up3d(ws)) return (int)blocks3d_w(ws);
   return kRedBlocks;
 }
@@ -1719,6 +1746,16 @@ hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const d
 // ---------------------------------------------------------------------------
 // Variable-coefficient set-up
 // ---------------------------------------------------------------------------
+// Face coefficients of the tiled 2D levels.
+template <typename T>
+static void launch_coef2d(hipStream_t st, PoissonWS &ws) {
+  for (int l = 0; l < ws.lc; ++l)
+    if (ws.vtx[l] > 0)
+      hipLaunchKernelGGL((k_vc_coef2d<T>), grid_for(ws.lev[l].lay), dim3(kBX, kBY), 0, st, ws.lev[l].lay, ws.bnd,
+                         (T)ws.lev[l].ih2[0], (T)ws.lev[l].ih2[1], (const T *)ws.rho[l], (T *)ws.cf[l][0],
+                         (T *)ws.cf[l][1], (T *)ws.cf[l][2], ws.met);
+}
+
 template <int DIM, typename T>
 static hipError_t set_beta_dim(hipStream_t st, PoissonWS &ws) {
   const dim3 bb(kBX, kBY);
@@ -1734,12 +1771,7 @@ static hipError_t set_beta_dim(hipStream_t st, PoissonWS &ws) {
       hipLaunchKernelGGL((k_vc_rho_down<DIM, T, T>), grid_for(Lc), bb, 0, st, Lf, Lc, (const T *)ws.rho[l],
                          (T *)ws.rho[l + 1]);
   }
-  if (DIM == 2)
-    for (int l = 0; l < ws.lc; ++l)
-      if (ws.vtx[l] > 0)
-        hipLaunchKernelGGL((k_vc_coef2d<T>), grid_for(ws.lev[l].lay), bb, 0, st, ws.lev[l].lay, ws.bnd,
-                           (T)ws.lev[l].ih2[0], (T)ws.lev[l].ih2[1], (const T *)ws.rho[l], (T *)ws.cf[l][0],
-                           (T *)ws.cf[l][1], (T *)ws.cf[l][2]);
+  if (DIM == 2) launch_coef2d<T>(st, ws);
   launch_coarse_setup<DIM, T>(st, ws);
   return hipGetLastError();
 }
@@ -1773,6 +1805,7 @@ static hipError_t set_metric_t(hipStream_t st, PoissonWS &ws) {
     }
   }
   ws.vc = 1;
+  launch_coef2d<T>(st, ws);
   launch_coarse_setup<2, T>(st, ws);
   return hipGetLastError();
 }
