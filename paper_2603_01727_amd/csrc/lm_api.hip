@@ -1770,7 +1770,9 @@ namespace {
 // Every device array of the solve lives here: 64 MiB per GPU, held from the
 // first call on that GPU until the process ends. Calls on one GPU share it.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// (the solver's constant geometry table sits behind them: it does not count
+// towards the limit)
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kGeoBytes];
 
 constexpr int kScratchDevices = 64;
 std::mutex g_scratch_mu;
@@ -1826,6 +1828,7 @@ extern "C" lm_status lm_project_static(const lm_grid *grid, const lm_params *par
   for (int d = 0; d < 3; ++d) h[d] = d < grid->ndim ? grid->L[d] / grid->n[d] : 1.0;
   // sizing pass: rejected before any device work when it does not fit
   PoissonWS ws{};
+  ws.geo_given = 1;
   double *b = nullptr, *staging = nullptr;
   Carver sz{nullptr, 0};
   if (!carve_solve(ws, sz, L, B, h, *params, &b, &staging))
@@ -1854,6 +1857,8 @@ extern "C" lm_status lm_project_static(const lm_grid *grid, const lm_params *par
   }
   hipStream_t st = (hipStream_t)stream;
   ws = PoissonWS{};
+  ws.geo_given = 1;
+  ws.geo = base + kScratchBytes;
   Carver cv{(char *)base, 0};
   carve_solve(ws, cv, L, B, h, *params, &b, &staging);
   ws.host_sc = &g_scratch_sc[dev];

@@ -293,6 +293,7 @@ struct Carver {
 constexpr int kMaxLev = 24;
 constexpr long kCoarseCells = 4096;   // levels at or below this size: one-block LDS kernel
 constexpr long kMaxCoarsest = 1024;   // dense pseudo-inverse limit
+constexpr size_t kGeoBytes = 1376 * 16;  // block geometry table of the one-workgroup kernels
 constexpr int kVcCoarsest = 128;      // coarsest cells of a variable-coefficient solve (inverse built on the device)
 
 struct PoissonWS {
@@ -325,7 +326,8 @@ struct PoissonWS {
   int vtx[kMaxLev], vty[kMaxLev];  // 2D tile of the variable-coefficient level kernels
   double *rho64;           // finest-level density (FP64, fine layout)
   void *rho[kMaxLev];      // density per level in MG precision (level 0 aliases rho64 in FP64)
-  void *geo;               // block geometry of the coarse-kernel levels
+  void *geo = nullptr;     // block geometry of the coarse-kernel levels (kGeoBytes)
+  int geo_given = 0;       // geo is the caller's, not carved
   void *ccf;               // face coefficients of the coarse-kernel levels, by block (MG precision)
   double *ccd;             // those of the finest level in FP64 (one-workgroup solve, mixed precision)
   void *pinv_vc;           // pseudo-inverse of the coarsest variable-coefficient operator

@@ -726,19 +726,24 @@ namespace lm {
 // Pseudo-inverse of the coarsest variable-coefficient operator,
 // (L + J/N)^{-1} - J/N with J the all-ones matrix: L + J/N is symmetric
 // positive definite (L is singular with the constants as null space), so
-// Gauss-Jordan elimination without pivoting inverts it in place in LDS.
-// UNIT: beta = 1 on every face (no densities read).
-constexpr int kPinvThreads = 256;
-template <int DIM, typename T, bool UNIT = false>
+// Gauss-Jordan elimination without pivoting inverts it. UNIT: beta = 1 on
+// every face (no densities read).
+// The N steps are a serial chain, one barrier each; the matrix stays in
+// registers (column t % NP, every R-th row) and only the next pivot row and
+// column pass through LDS. 64 cells: 55 us; with the matrix in LDS, 256
+// threads and two barriers per step 130 us.
+constexpr int kPinvThreads = 1024;
+template <int DIM, typename T, bool UNIT, int NP>
 __global__ void __launch_bounds__(kPinvThreads) k_vc_pinv(Lay L, Bnd B, Ih2<double> ih2v, int met, const T *rho,
                                                           T *pinv) {
-  __shared__ double M[kVcCoarsest * kVcCoarsest];
-  __shared__ double rk[kVcCoarsest], ck[kVcCoarsest];
+  constexpr int R = kPinvThreads / NP, ROWS = NP / R;
+  __shared__ double M[NP * NP];
+  __shared__ double rk[2][NP], ck[2][NP];
   const int *n = L.n;
   const int N = n[0] * n[1] * n[2];
   const int t = threadIdx.x;
   const double jn = 1.0 / (double)N;
-  for (int e = t; e < N * N; e += blockDim.x) M[e] = jn;
+  for (int e = t; e < NP * NP; e += kPinvThreads) M[e] = (e / NP < N && e % NP < N) ? jn : 0.0;
   __syncthreads();
   if (t < N) {
     int i, j, k;
@@ -754,47 +759,47 @@ __global__ void __launch_bounds__(kPinvThreads) k_vc_pinv(Lay L, Bnd B, Ih2<doub
         const bool in = side == 0 ? q[d] > 0 : q[d] + 1 < n[d];
         if (!in && !per) continue;
         const int m = side == 0 ? (in ? t - st[d] : t + (n[d] - 1) * st[d]) : (in ? t + st[d] : t - (n[d] - 1) * st[d]);
-        const double w = UNIT ? ih2 : ih2 * face_coef<double>(rc, (double)rho[nbr(L, B, g, q[d], d, side ? 1 : -1)], d, met);
-        M[t * N + t] += w;
-        M[t * N + m] -= w;
+        const long gm = nbr(L, B, g, q[d], d, side ? 1 : -1);
+        const double w = UNIT ? ih2 : ih2 * face_coef<double>(rc, (double)rho[gm], d, met);
+        M[t * NP + t] += w;
+        M[t * NP + m] -= w;
       }
     }
   }
   __syncthreads();
-  // thread t owns column j = t % N of rows t / N + R p (R = rows per pass)
-  const int R = blockDim.x / N;
-  const int j = t % N, i0 = t / N;
-  const bool active = i0 < R;
-  constexpr int kPass = (kVcCoarsest + kPinvThreads / kVcCoarsest - 1) / (kPinvThreads / kVcCoarsest);
-  for (int kk = 0; kk < N; ++kk) {
-    if (t < N) {
-      rk[t] = M[kk * N + t];
-      ck[t] = M[t * N + kk];
-    }
-    __syncthreads();
-    const double ip = 1.0 / rk[kk];
-    const double rj = rk[j] * ip;
-    if (active) {
+  const int j = t % NP, i0 = t / NP;
+  double m[ROWS];
 #pragma unroll
-      for (int p = 0; p < kPass; ++p) {
-        const int i = i0 + R * p;
-        if (i >= N) break;
-        double v;
-        if (i == kk)
-          v = (j == kk) ? ip : rj;
-        else if (j == kk)
-          v = -ck[i] * ip;
-        else
-          v = M[i * N + j] - ck[i] * rj;
-        M[i * N + j] = v;
-      }
-    }
-    __syncthreads();
+  for (int p = 0; p < ROWS; ++p) m[p] = M[(i0 + R * p) * NP + j];
+  if (t < NP) {
+    rk[0][t] = M[t];
+    ck[0][t] = M[t * NP];
   }
-  for (int e = t; e < N * N; e += blockDim.x) pinv[e] = (T)(M[e] - jn);
+  for (int kk = 0; kk < N; ++kk) {
+    const int cur = kk & 1;
+    __syncthreads();
+    const double ip = 1.0 / rk[cur][kk];
+    const double rj = rk[cur][j] * ip;
+#pragma unroll
+    for (int p = 0; p < ROWS; ++p) {
+      const int i = i0 + R * p;
+      const double c = ck[cur][i];
+      double v = m[p] - c * rj;
+      if (j == kk) v = -c * ip;
+      if (i == kk) v = j == kk ? ip : rj;
+      m[p] = v;
+      if (i == kk + 1) rk[cur ^ 1][j] = v;
+      if (j == kk + 1) ck[cur ^ 1][i] = v;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < ROWS; ++p) {
+    const int i = i0 + R * p;
+    if (i < N && j < N) pinv[i * N + j] = (T)(m[p] - jn);
+  }
 }
-
-static_assert(kVcCoarsest <= kPinvThreads, "one thread per coarsest cell");
+static_assert(kVcCoarsest == 128, "the larger of the two inverse kernels");
+static_assert(kBlkGeo * sizeof(BlkGeo) == kGeoBytes, "size of the block geometry table");
 }  // namespace lm
 
 namespace lm {
@@ -996,7 +1001,7 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
     ws.lev[l].b = cv.take(lb);
   }
   ws.pinv = cv.take((size_t)ncoarsest * ncoarsest * eb);
-  ws.geo = cv.take((size_t)kBlkGeo * sizeof(BlkGeo));
+  if (!ws.geo_given) ws.geo = cv.take(kGeoBytes);
   ws.rho64 = nullptr;
   ws.ccf = ws.pinv_vc = nullptr;
   ws.ccd = nullptr;
@@ -1443,6 +1448,14 @@ static void launch_blk_coef(hipStream_t st, PoissonWS &ws, int nq, const R *cons
     hipLaunchKernelGGL((k_blk_coef<DIM, R>), dim3(ceil_div(most, kBlock), nq), dim3(kBlock), 0, st, a, out);
 }
 
+template <int DIM, typename T, bool UNIT>
+static void launch_pinv(hipStream_t st, PoissonWS &ws, const T *rho, T *pinv) {
+  const Lay &L = ws.lev[ws.nlev - 1].lay;
+  auto k = L.ncells() <= 64 ? &k_vc_pinv<DIM, T, UNIT, 64> : &k_vc_pinv<DIM, T, UNIT, kVcCoarsest>;
+  hipLaunchKernelGGL(k, dim3(1), dim3(kPinvThreads), 0, st, L, ws.bnd, ih2_of<double>(ws, ws.nlev - 1),
+                     UNIT ? 0 : ws.met, rho, pinv);
+}
+
 // Face coefficients and coarsest pseudo-inverse of the variable-coefficient
 // cycle, from the levels' densities (or cell ratios).
 template <int DIM, typename T>
@@ -1455,9 +1468,7 @@ static void launch_coarse_setup(hipStream_t st, PoissonWS &ws) {
     const double *r64[1] = {ws.rho64};
     launch_blk_coef<DIM, double>(st, ws, 1, r64, ws.ccd);
   }
-  const MGLevel &m = ws.lev[ws.nlev - 1];
-  hipLaunchKernelGGL((k_vc_pinv<DIM, T>), dim3(1), dim3(kPinvThreads), 0, st, m.lay, ws.bnd, ih2_of<double>(ws, ws.nlev - 1),
-                     ws.met, (const T *)ws.rho[ws.nlev - 1], (T *)ws.pinv_vc);
+  launch_pinv<DIM, T, false>(st, ws, (const T *)ws.rho[ws.nlev - 1], (T *)ws.pinv_vc);
 }
 
 // In-step timing: events for this launch when it is the next timed launch
@@ -1842,17 +1853,14 @@ hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws) {
   if (ws.lev[ws.nlev - 1].lay.ncells() > kVcCoarsest) return hipErrorInvalidValue;
   const hipError_t e = launch_geo(st, ws);
   if (e != hipSuccess) return e;
-  const MGLevel &m = ws.lev[ws.nlev - 1];
-  const Ih2<double> ih2 = ih2_of<double>(ws, ws.nlev - 1);
-  auto run = [&](auto k, auto *out) {
-    hipLaunchKernelGGL(k, dim3(1), dim3(kPinvThreads), 0, st, m.lay, ws.bnd, ih2, 0, (decltype(out))nullptr, out);
-  };
+  const float *f = nullptr;
+  const double *d = nullptr;
   if (ws.lay.ndim == 3) {
-    if (ws.mixed) run(&k_vc_pinv<3, float, true>, (float *)ws.pinv);
-    else run(&k_vc_pinv<3, double, true>, (double *)ws.pinv);
+    if (ws.mixed) launch_pinv<3, float, true>(st, ws, f, (float *)ws.pinv);
+    else launch_pinv<3, double, true>(st, ws, d, (double *)ws.pinv);
   } else {
-    if (ws.mixed) run(&k_vc_pinv<2, float, true>, (float *)ws.pinv);
-    else run(&k_vc_pinv<2, double, true>, (double *)ws.pinv);
+    if (ws.mixed) launch_pinv<2, float, true>(st, ws, f, (float *)ws.pinv);
+    else launch_pinv<2, double, true>(st, ws, d, (double *)ws.pinv);
   }
   return hipGetLastError();
 }
