@@ -48,7 +48,11 @@ struct Fused3DArgs {
   int np;
 };
 
-__device__ inline int wrap_p(int g, int n) { return g < 0 ? g + n : (g >= n ? g - n : g); }
+// (a frame may be several periods wide on a small level)
+__device__ inline int wrap_p(int g, int n) {
+  const int r = g % n;
+  return r < 0 ? r + n : r;
+}
 // Plane index of the loads, which stay within [-n, 2n) on the fused levels
 // (chunks reach at most 13 planes past either end; levels have >= 16).
 __device__ inline int wrap_any(int g, int n) { return g < 0 ? g + n : (g >= n ? g - n : g); }

@@ -47,7 +47,6 @@ constexpr int kRedBlocks = 1024;   // grid of the grid-stride reduction kernels
 // for sizes that neither divides.
 constexpr int TX = 64, TY = 16;
 constexpr int TXS = 32, TYS = 8;
-constexpr long kFused3DMinCells = 1L << 15;  // smaller 3D levels run the per-half-sweep kernels
 
 Lay make_layout(int ndim, const int n[3], int elem_bytes) {
   Lay L;
@@ -877,16 +876,18 @@ static int ti3(int nu, bool down, bool extra) {
 }
 static int tiles3(const Lay &L, int ti, int d) { return (L.n[d] + ti - 1) / ti; }
 
-// Depth of the z chunk (a multiple of 4): the level is split into as many chunks as
-// keep about one block per block slot of the chip (256 CUs, two 512-thread
-// blocks each), but no chunk shallower than 16 planes: every chunk reads
-// 2H halo planes beyond its own.
+// Depth of the z chunk (a multiple of 4: the chunks start on the kernels'
+// LDS buffer order): as many chunks as keep about one block per block slot
+// of the chip (256 CUs, two 512-thread blocks each). Every chunk marches
+// through 2H halo planes beyond its own, so a level that cannot fill the
+// chip takes the shallowest chunks: its time is that of one block's march
+// (about 0.55 us a plane step), whatever their number. 32^3 level: chunks of
+// 4 planes 7.7 us per leg, of 16 planes 13.3 us.
 static int tz3_of(const Lay &L, int ti) {
   const long tiles = (long)tiles3(L, ti, 0) * tiles3(L, ti, 1);
-  long nchunk = std::max(1L, 512L / tiles);
-  int tz = (int)((L.n[2] + nchunk - 1) / nchunk);
-  tz = std::max(16, (tz + 3) & ~3);  // chunks start on multiples of 4 (the kernels' LDS buffer order)
-  return tz;
+  const long nchunk = std::max(1L, 512L / tiles);
+  const int tz = (int)((L.n[2] + nchunk - 1) / nchunk);
+  return (tz + 3) & ~3;
 }
 
 // Blocks of one fused 3D launch on layout L with owned tile edge ti.
@@ -895,11 +896,14 @@ static long blocks3d(const Lay &L, int ti) {
   return (long)tiles3(L, ti, 0) * tiles3(L, ti, 1) * ((L.n[2] + tz - 1) / tz);
 }
 
-// Level l runs the fused 3D kernels (fully periodic grids, even sizes).
+// Level l runs the fused 3D kernels (fully periodic grids, even sizes, every
+// level above the one-workgroup cycle: 40 x 24 x 28, FP32, two launches of 8
+// us against ten of 4.6 us; the march's plane index wraps once, so at least
+// 16 planes).
 static bool fused3d(const PoissonWS &ws, int l) {
   const Lay &L = ws.lev[l].lay;
   return !ws.vc && L.ndim == 3 && ws.bnd.all_periodic && ws.nu >= 1 && ws.nu <= 2 && l < ws.lc &&
-         L.ncells() >= kFused3DMinCells && L.n[0] % 2 == 0 && L.n[1] % 2 == 0 && L.n[2] % 2 == 0 &&
+         L.n[0] % 2 == 0 && L.n[1] % 2 == 0 && L.n[2] % 2 == 0 &&
          L.n[2] >= 16;
 }
 

@@ -106,3 +106,13 @@ def test_ragged_tiles_density(n, bc, precision):
 @pytest.mark.parametrize("n", [(96, 96), (88, 72), (24, 208)], ids=str)
 def test_tiles_stretched(n, precision):
     _check(n, WALLS, precision, stretch=2.0)
+
+
+# fused 3D levels: a small finest level, frames several periods wide, the
+# fewest planes the march takes, chunks that do not divide the planes, and
+# one plane pair too few (unfused)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nu", [1, 2])
+@pytest.mark.parametrize("n", [(40, 24, 28), (8, 48, 16), (8, 8, 80), (12, 20, 24), (32, 40, 36), (32, 40, 8)], ids=str)
+def test_fused_3d_levels(n, nu, precision):
+    _check(n, None, precision, nu=nu)
