@@ -51,13 +51,13 @@ struct lm_ctx {
   double *side_store[3][2][7];  // v[3], Z, H, F, wall flags (bytes)
   double *staging;
   size_t staging_bytes;
-  int *dflags;           // [0] bad T, [1] non-finite
+  int *dflags;           // [0] bad T
   double *dscalar;       // [0] CFL max rate
   PoissonWS pws;
-  int *hflags;           // pinned
+  int *hflags;           // pinned: [0] copy of dflags[0], [1] a non-finite velocity (written by the projection)
   double *hscalar;       // pinned
-  SolveLog *dlog;        // outcome of the step's two solves (one-block solver), checked after the step
-  SolveLog *hlog;        // pinned copy
+  SolverScalars host_sc; // outcome of the last solve
+  SolveLog *hlog;        // outcome of the step's two solves (one-block solver; pinned, written by its kernel)
   int have_state, have_prev;
   double time;
   long long total_iters;
@@ -403,7 +403,6 @@ bool carve(lm_ctx *c, Carver &cv, std::string *err) {
   c->staging = (double *)cv.take(c->staging_bytes);
   c->dflags = (int *)cv.take(64);
   c->dscalar = (double *)cv.take(64);
-  c->dlog = (SolveLog *)cv.take(2 * sizeof(SolveLog));
   {
     const bool adj = c->prm.with_adjoint;
     auto take = [&](bool on) { return adj && on ? (double *)cv.take(ab) : nullptr; };
@@ -561,11 +560,13 @@ lm_status lm_init_grid(const lm_grid *grid, const lm_params *params, void *ws, s
   hipError_t e = hipHostMalloc((void **)&c->hflags, 64);
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->hscalar, 64);
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->hlog, 2 * sizeof(SolveLog));
-  if (e == hipSuccess) e = hipHostMalloc((void **)&c->pws.host_sc, sizeof(SolverScalars));
+  if (e == hipSuccess) e = hipHostMalloc((void **)&c->pws.host_out, sizeof(HostSolve));
   if (e != hipSuccess) {
     lm_destroy(c);
     return init_fail(LM_EHIP, std::string("hipHostMalloc: ") + hipGetErrorString(e));
   }
+  memset((void *)c->pws.host_out, 0, sizeof(HostSolve));
+  c->pws.host_sc = &c->host_sc;
   // zero the whole carved region once (ghost layers, padding, scalars)
   e = hipMemsetAsync(base, 0, cv.off, c->st);
   if (e != hipSuccess) {
@@ -900,29 +901,31 @@ static lm_status do_stage(lm_ctx *c, int corrector, int &iters, double &relres, 
   }
   int conv = 0;
   const int expect = c->last_iters[corrector];
-  // the one-block solver leaves its outcome on the device; lm_step reads
+  // the one-block solver leaves its outcome in pinned memory; lm_step reads
   // both stages' after the step (one wait per step instead of three)
-  SolveLog *log = c->pws.block_pcg ? c->dlog + corrector : nullptr;
+  SolveLog *log = c->pws.block_pcg ? c->hlog + corrector : nullptr;
+  double *P_out = corrector ? c->P[c->inxt] : c->P[c->istar];
+  // queued before the host knows the outcome: gated on it, except behind the
+  // one-block solver, whose failure voids the step anyway
+  auto project = [&]() {
+    return launch_project(c->st, L, c->bnd, c->phys, c->sides, c->M, c->pws.x, out.rho, c->pws.sc, out.F, out.v,
+                          P_out, c->hflags + 1, log == nullptr);
+  };
   HIPCHK(c, poisson_solve(c->st, c->pws, c->b, x0, c->prm.poisson_rtol, c->prm.poisson_maxit, expect, &iters,
-                          &relres, &conv, log));
+                          &relres, &conv, log, project));
   if (!log) {
     compat = c->pws.host_sc->mean_b;
     c->last_iters[corrector] = iters > 0 ? iters : 1;
     c->total_iters += iters;
     if (!conv) return fail(c, LM_ENOCONV, "Poisson solver did not reach poisson_rtol");
   }
-  double *P_out = corrector ? c->P[c->inxt] : c->P[c->istar];
-  HIPCHK(c, launch_project(c->st, L, c->bnd, c->phys, c->sides, c->M, c->pws.x, out.rho, c->pws.sc, out.F, out.v,
-                           P_out, c->dflags + 1));
   return LM_OK;
 }
 
 // Reads back the outcome of both stage solves when the one-workgroup solver
-// deferred it to the device log (stage solves then skip their own host
+// deferred it to the log (stage solves then skip their own host
 // check), synchronising the stream; otherwise only synchronises.
 static lm_status read_solve_logs(lm_ctx *c, int it[2], double rr[2], double cm[2]) {
-  if (c->pws.block_pcg)
-    HIPCHK(c, hipMemcpyAsync(c->hlog, c->dlog, 2 * sizeof(SolveLog), hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
   if (!c->pws.block_pcg) return LM_OK;
   for (int q = 0; q < 2; ++q) {
@@ -946,15 +949,15 @@ lm_status lm_step(lm_ctx *c, int nsteps, lm_step_stats *stats) {
   double rr[2] = {0, 0}, cm[2] = {0, 0};
   for (int n = 0; n < nsteps; ++n) {
     set_step_weights(c);
-    HIPCHK(c, hipMemsetAsync(c->dflags + 1, 0, 4, c->st));
+    c->hflags[1] = 0;  // (nothing queued before writes it any more: every step ends with a wait)
     lm_status s = do_stage(c, 0, it[0], rr[0], cm[0]);
     if (s == LM_OK) s = do_stage(c, 1, it[1], rr[1], cm[1]);
     if (s == LM_OK) {
-      HIPCHK(c, hipMemcpyAsync(c->hflags + 1, c->dflags + 1, 4, hipMemcpyDeviceToHost, c->st));
       s = read_solve_logs(c, it, rr, cm);
       if (s == LM_OK && c->hflags[1]) s = fail(c, LM_ENONFINITE, "non-finite velocity after the step");
     }
     if (s != LM_OK) {
+      (void)hipStreamSynchronize(c->st);
       if (stats) {
         stats->steps = done;
         stats->dt = c->dt_last;
@@ -1027,9 +1030,16 @@ lm_status lm_project(lm_ctx *c, lm_project_args *a) {
   double relres = 0;
   const double rtol = a->rtol > 0 ? a->rtol : c->prm.poisson_rtol;
   c->pws.vc = c->pws.met || a->rho != nullptr;
-  // a standalone solve: zero start in solver scratch, the state untouched
+  // a standalone solve: zero start in solver scratch, the state untouched;
+  // the shift to zero mean (in place) and the copy to a device array are
+  // queued behind it, gated on its outcome
+  auto finish = [&]() -> hipError_t {
+    hipError_t q = launch_shift(c->st, L, c->pws.x, c->pws.sc, c->pws.x, 1);
+    if (q == hipSuccess && a->P && a->mem == LM_DEVICE) q = launch_unpack(c->st, L, c->pws.x, a->P, -1, c->pws.sc);
+    return q;
+  };
   const hipError_t e = poisson_solve(c->st, c->pws, c->b, nullptr, rtol, c->prm.poisson_maxit, 0, &iters,
-                                     &relres, &conv);
+                                     &relres, &conv, nullptr, finish);
   c->pws.vc = c->pws.met;
   HIPCHK(c, e);
   if (a->rho && c->pws.host_sc->rho_bad) return fail(c, LM_EINVAL, "rho must be positive and finite");
@@ -1037,8 +1047,7 @@ lm_status lm_project(lm_ctx *c, lm_project_args *a) {
   a->relres = relres;
   a->mean_b = c->pws.host_sc->mean_b;
   if (!conv) return fail(c, LM_ENOCONV, "Poisson solver did not reach rtol");
-  HIPCHK(c, launch_shift(c->st, L, c->pws.x, c->pws.sc, c->pws.x));  // zero mean, in place
-  if (a->P) return copy_out(c, c->pws.x, a->P, -1, a->mem);
+  if (a->P && a->mem == LM_HOST) return copy_out(c, c->pws.x, a->P, -1, a->mem);
   return LM_OK;
 }
 
@@ -1084,7 +1093,7 @@ void lm_destroy(lm_ctx *c) {
   if (c->hflags) (void)hipHostFree(c->hflags);
   if (c->hscalar) (void)hipHostFree(c->hscalar);
   if (c->hlog) (void)hipHostFree(c->hlog);
-  if (c->pws.host_sc) (void)hipHostFree(c->pws.host_sc);
+  if (c->pws.host_out) (void)hipHostFree(c->pws.host_out);
   delete c;
 }
 
@@ -1117,7 +1126,7 @@ extern "C" lm_status lm_bench_kernel(lm_ctx *c, int which, int reps, double *avg
                           c->b, c->pws.partials, c->pws.sc);
       case 7:
         return launch_project(c->st, c->lay, c->bnd, c->phys, c->sides, c->M, c->pws.x, S.rho, c->pws.sc, S.F,
-                              S.v, c->P[c->istar], c->dflags + 1);
+                              S.v, c->P[c->istar], c->hflags + 1);
       default: return poisson_bench_launch(c->st, c->pws, which);
     }
   };

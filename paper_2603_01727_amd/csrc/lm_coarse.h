@@ -691,6 +691,8 @@ struct BlockPCGArgs {
   const double *cd;         // FP64 coefficient sets of the finest level (variable coefficients)
   SolverScalars *sc;
   SolveLog *log;            // optional copy of the outcome (deferred checks)
+  HostSolve *host;          // optional: pinned memory the host watches for the scalars, with their number
+  unsigned seq;
 };
 
 // Sums of three values over the NT threads, in every thread. With 4
@@ -727,6 +729,21 @@ __device__ inline void block_sum3(double &v0, double &v1, double &v2, double *re
   v2 = red[3 * NP + 2];
 }
 
+// The outcome in sc for the host (one thread).
+template <typename T>
+__device__ inline void tell_outcome(const BlockPCGArgs<T> &a) {
+  const SolverScalars *sc = a.sc;
+  if (a.log) {
+    a.log->rr = sc->rr;
+    a.log->cc = sc->cc;
+    a.log->mean_b = sc->mean_b;
+    a.log->iters = sc->iters;
+    a.log->done = sc->done;
+    a.log->nonconv = sc->nonconv;
+  }
+  if (a.host) host_write(a.host, sc, a.seq);
+}
+
 template <int DIM, typename T, bool CF, bool PLAIN>
 __global__ void __launch_bounds__(kBlkThreads<DIM>) k_pcg_block(BlockPCGArgs<T> a) {
   constexpr int NC = 1 << DIM, NT = kBlkThreads<DIM>;
@@ -739,18 +756,12 @@ __global__ void __launch_bounds__(kBlkThreads<DIM>) k_pcg_block(BlockPCGArgs<T> 
   const int tid = threadIdx.x;
   if (a.rho && sc->rho_bad) {  // invalid density: the solve ends at once
     if (tid == 0) {
+      sc->rr = sc->cc = 0.0;
       sc->done = 1;
       sc->iters = 0;
       sc->nonconv = 1;
       sc->zero = 0;
-      if (a.log) {
-        a.log->done = 1;
-        a.log->nonconv = 1;
-        a.log->iters = 0;
-        a.log->rr = 0.0;
-        a.log->cc = 0.0;
-        a.log->mean_b = sc->mean_b;
-      }
+      tell_outcome(a);
     }
     return;
   }
@@ -984,14 +995,7 @@ __global__ void __launch_bounds__(kBlkThreads<DIM>) k_pcg_block(BlockPCGArgs<T> 
     sc->zero = (cc == 0.0);
     sc->nonconv = nonconv;
     sc->mean_x = sx / a.mean_w;
-    if (a.log) {
-      a.log->rr = rr;
-      a.log->cc = cc;
-      a.log->mean_b = sc->mean_b;
-      a.log->iters = iters;
-      a.log->done = done;
-      a.log->nonconv = nonconv;
-    }
+    tell_outcome(a);
   }
 }
 

@@ -78,6 +78,9 @@ __device__ inline long nbr(const Lay &L, const Bnd &B, long c, int q, int d, int
   return B.periodic[d] ? c + (long)(L.n[d] - 1) * L.s[d] : -1;
 }
 
+// The solve whose scalars these are has ended with a solution.
+__device__ inline bool solved(const SolverScalars *sc) { return sc->done && !sc->nonconv; }
+
 __device__ inline int coord(const CellPos &p, int d) { return d == 0 ? p.i : (d == 1 ? p.j : p.k); }
 
 // Sum over a block of kBlock threads; the result is valid in thread 0.

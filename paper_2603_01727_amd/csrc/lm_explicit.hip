@@ -930,7 +930,8 @@ struct ProjArgs {
   const double *x, *rho_new;
   const SolverScalars *sc;
   double *F[3], *v[3], *P_out;
-  int *nonfinite;
+  int *nonfinite;  // set to 1 when a velocity is not finite (host or device memory)
+  int gated;       // run only when the solve has ended with a solution
 };
 
 // F_d = G_d - delta_1 P on interior faces and the prescribed flux on
@@ -939,6 +940,7 @@ struct ProjArgs {
 // extrapolation at non-periodic sides (Eq 3.27-3.28); P stored zero-mean.
 template <int DIM, bool MET = false>
 __global__ void __launch_bounds__(kBlock) k_project(Lay L, Bnd B, Phys P, Sides sd, ProjArgs a) {
+  if (a.gated && !solved(a.sc)) return;
   CellPos p;
   if (!cell_of_thread(L, p)) return;
   const long c = p.c;
@@ -987,13 +989,13 @@ __global__ void __launch_bounds__(kBlock) k_project(Lay L, Bnd B, Phys P, Sides 
     bad |= !isfinite(v);
   }
   if (a.P_out) a.P_out[c] = (x == nullptr || a.sc->zero) ? 0.0 : xc - a.sc->mean_x;
-  if (bad) atomicOr(a.nonfinite, 1);
+  if (bad) *a.nonfinite = 1;
 }
 
 hipError_t launch_project(hipStream_t st, const Lay &L, const Bnd &B, const Phys &P, const Sides &sd,
                           double *const M[3], const double *x, const double *rho_new,
                           const SolverScalars *sc, double *F[3], double *v[3], double *P_out,
-                          int *nonfinite) {
+                          int *nonfinite, int gated) {
   ProjArgs a;
   for (int i = 0; i < 3; ++i) {
     a.M[i] = M[i];
@@ -1005,6 +1007,7 @@ hipError_t launch_project(hipStream_t st, const Lay &L, const Bnd &B, const Phys
   a.sc = sc;
   a.P_out = P_out;
   a.nonfinite = nonfinite;
+  a.gated = gated;
   dim3 g = grid_for(L), bl(kBX, kBY);
   if (L.ndim == 3)
     hipLaunchKernelGGL(k_project<3>, g, bl, 0, st, L, B, P, sd, a);
@@ -1208,7 +1211,9 @@ hipError_t launch_pc_err(hipStream_t st, const Lay &L, int reacting, const Level
 
 // face_dir < 0: cell field (nz, ny, nx). face_dir = d: face array with
 // n_d + 1 entries along d, entry f stored at padded cell f - 1 (its high face).
-__global__ void __launch_bounds__(kBlock) k_pack(Lay L, const double *src, double *dst, int fd, int unpack) {
+__global__ void __launch_bounds__(kBlock) k_pack(Lay L, const double *src, double *dst, int fd, int unpack,
+                                                 const SolverScalars *gate) {
+  if (gate && !solved(gate)) return;
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   long m[3] = {L.n[0], L.n[1], L.n[2]};
   if (fd >= 0) m[fd] += 1;
@@ -1228,14 +1233,17 @@ __global__ void __launch_bounds__(kBlock) k_pack(Lay L, const double *src, doubl
 hipError_t launch_pack(hipStream_t st, const Lay &L, const double *src, double *dst, int face_dir) {
   long m = L.ncells();
   if (face_dir >= 0) m = m / L.n[face_dir] * (L.n[face_dir] + 1);
-  hipLaunchKernelGGL(k_pack, dim3(ceil_div(m, kBlock)), dim3(kBlock), 0, st, L, src, dst, face_dir, 0);
+  hipLaunchKernelGGL(k_pack, dim3(ceil_div(m, kBlock)), dim3(kBlock), 0, st, L, src, dst, face_dir, 0,
+                     (const SolverScalars *)nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(hipStream_t st, const Lay &L, const double *src, double *dst, int face_dir) {
+hipError_t launch_unpack(hipStream_t st, const Lay &L, const double *src, double *dst, int face_dir,
+                         const SolverScalars *gate) {
   long m = L.ncells();
   if (face_dir >= 0) m = m / L.n[face_dir] * (L.n[face_dir] + 1);
-  hipLaunchKernelGGL(k_pack, dim3(ceil_div(m, kBlock)), dim3(kBlock), 0, st, L, src, dst, face_dir, 1);
+  hipLaunchKernelGGL(k_pack, dim3(ceil_div(m, kBlock)), dim3(kBlock), 0, st, L, src, dst, face_dir, 1,
+                     gate);
   return hipGetLastError();
 }
 
@@ -1278,15 +1286,18 @@ hipError_t launch_mean(hipStream_t st, const Lay &L, const double *a, double *pa
 }
 
 // out = x - mean(x) (zero-mean pressure), or 0 when the right-hand side vanished.
-__global__ void __launch_bounds__(kBlock) k_shift(Lay L, const double *x, const SolverScalars *sc, double *out) {
+__global__ void __launch_bounds__(kBlock) k_shift(Lay L, const double *x, const SolverScalars *sc, double *out,
+                                                  int gated) {
+  if (gated && !solved(sc)) return;
   CellPos p;
   if (!cell_of_thread(L, p)) return;
   out[p.c] = sc->zero ? 0.0 : x[p.c] - sc->mean_x;
 }
 
-hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const SolverScalars *sc, double *out) {
+hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const SolverScalars *sc, double *out,
+                        int gated) {
   dim3 g = grid_for(L), bl(kBX, kBY);
-  hipLaunchKernelGGL(k_shift, g, bl, 0, st, L, x, sc, out);
+  hipLaunchKernelGGL(k_shift, g, bl, 0, st, L, x, sc, out, gated);
   return hipGetLastError();
 }
 

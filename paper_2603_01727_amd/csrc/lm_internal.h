@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -116,6 +117,13 @@ struct SolverScalars {
   int rho_bad;                     // a density given for beta = 1/rho_f is not positive and finite
 };
 
+// Outcome of a pressure solve in pinned host memory, written by a kernel: the
+// scalars, then the number the host waits for.
+struct HostSolve {
+  SolverScalars sc;
+  unsigned seq;
+};
+
 // Outcome of one pressure solve, written on the device when the host
 // checks it later (after the step) instead of waiting for it.
 struct SolveLog {
@@ -170,11 +178,11 @@ hipError_t launch_rhs(hipStream_t st, const Lay &L, const Bnd &B, const Phys &P,
 hipError_t launch_project(hipStream_t st, const Lay &L, const Bnd &B, const Phys &P, const Sides &sd,
                           double *const M[3], const double *x, const double *rho_new,
                           const SolverScalars *sc, double *F[3], double *v[3], double *P_out,
-                          int *nonfinite);
+                          int *nonfinite, int gated = 0);
 hipError_t launch_pack(hipStream_t st, const Lay &L, const double *src_compact, double *dst_padded,
                        int face_dir);
 hipError_t launch_unpack(hipStream_t st, const Lay &L, const double *src_padded, double *dst_compact,
-                         int face_dir);
+                         int face_dir, const SolverScalars *gate = nullptr);
 hipError_t launch_pack_u8(hipStream_t st, const Lay &L, const unsigned char *src, unsigned char *dst);
 hipError_t launch_init_state(hipStream_t st, const Lay &L, const Phys &P, const Bnd &B,
                              const Sides &sd, int from_T, Level &lv, int *bad_flag);
@@ -274,7 +282,8 @@ hipError_t launch_adj_extrap(hipStream_t st, const Lay &L, const double *x1, con
 // y += (-sum_side y/h - sum_side Fb) dV/area (scratch: one double).
 hipError_t launch_adj_outflow(hipStream_t st, const Lay &L, const AdjPhys &P, int d, double *y, const double *Fb,
                               double *scratch);
-hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const SolverScalars *sc, double *out);
+hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const SolverScalars *sc, double *out,
+                        int gated = 0);
 
 // ---- Poisson (lm_solver.hip) -----------------------------------------------
 // Bump allocator over the caller workspace; with base == nullptr it only
@@ -319,7 +328,9 @@ struct PoissonWS {
   long np_max;
   double *partials;        // scratch partials of once-per-solve reductions
   SolverScalars *sc;       // device scalars
-  SolverScalars *host_sc;  // pinned host copy
+  SolverScalars *host_sc;  // host copy
+  HostSolve *host_out = nullptr;  // pinned memory a solve's last kernel writes its outcome to (NULL: copied instead)
+  unsigned seq = 0;        // number of the last outcome asked for
   // variable-coefficient form A P = sum_d delta_1 (beta delta_1 P), beta = 1/rho_f
   int vc_cap;              // arrays below reserved
   int vc;                  // the solve in progress uses beta = 1/rho_f
@@ -356,9 +367,12 @@ hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws);
 // when ws.block_pcg) the call returns once the solve is queued and its
 // outcome lands in *log on the device; iters, relres and converged are then
 // not written.
+// after (optional) queues the work that follows the solve on the stream; it
+// is queued before the host has read the outcome, possibly more than once,
+// so its kernels run only when solved(sc) holds (they take sc as their gate).
 hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const double *x0, double rtol,
                          int maxit, int expect_iters, int *iters, double *relres, int *converged,
-                         SolveLog *log = nullptr);
+                         SolveLog *log = nullptr, const std::function<hipError_t()> &after = nullptr);
 // Prepares a variable-coefficient solve from the density in ws.rho64 (fine
 // layout): the density on every level (2^d-cell averages), the coarse
 // levels' face coefficients and the coarsest pseudo-inverse. Sets

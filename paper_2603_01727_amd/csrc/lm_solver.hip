@@ -19,7 +19,8 @@
 // block sum those partials in the same fixed order (no atomics, no grid-wide
 // fences, bitwise reproducible). The convergence test runs on the device and
 // raises a flag that turns every later kernel into an immediate return; the
-// host queues iterations in batches and reads the flag once per batch.
+// host queues the expected iterations and reads the flag while the device
+// goes on with the work behind the solve, gated on its outcome.
 //
 // Levels. 2D levels run one LDS tile
 // kernel per level and direction with temporal blocking (nu red-black sweeps
@@ -32,6 +33,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -573,8 +575,10 @@ __global__ void __launch_bounds__(kBlock) k_cgcg_w(CGArgs a, double *w) {
 
 // Sum of x into partials (mean of the final solution).
 template <int DIM>
-__global__ void __launch_bounds__(kBlock) k_sum_x(Lay L, const double *x, double *part, const double *vol) {
+__global__ void __launch_bounds__(kBlock) k_sum_x(Lay L, const double *x, double *part, const double *vol,
+                                                  const SolverScalars *sc) {
   __shared__ double sh[kBlock / 64];
+  if (!sc->done) return;
   // four tiles' loads in flight per trip, four running sums combined in a
   // fixed order
   double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -594,10 +598,23 @@ __global__ void __launch_bounds__(kBlock) k_sum_x(Lay L, const double *x, double
   if (linear_tid() == 0) part[blockIdx.x] = r;
 }
 
-__global__ void __launch_bounds__(kBlock) k_fin_mean_x(const double *part, int np, double ncells, SolverScalars *sc) {
+// The scalars of a solve into the host's pinned memory, then their number.
+__device__ inline void host_write(HostSolve *host, const SolverScalars *sc, unsigned seq) {
+  host->sc = *sc;
+  __threadfence_system();
+  __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Mean of the solution of an ended solve; the scalars to the host's pinned
+// memory, if it waits there.
+__global__ void __launch_bounds__(kBlock) k_fin_mean_x(const double *part, int np, double ncells, SolverScalars *sc,
+                                                       HostSolve *host, unsigned seq) {
   __shared__ double sh[kBlock / 64];
-  const double s = sum_all(part, np, sh);
-  if (threadIdx.x == 0) sc->mean_x = s / ncells;
+  if (sc->done) {
+    const double s = sum_all(part, np, sh);
+    if (threadIdx.x == 0) sc->mean_x = s / ncells;
+  }
+  if (host && threadIdx.x == 0) host_write(host, sc, seq);
 }
 
 // ---------------------------------------------------------------------------
@@ -1486,9 +1503,14 @@ static bool timed_launch(const PoissonWS &ws, int which, hipEvent_t &e0, hipEven
   return true;
 }
 
+// An iteration is queued whole, or its head alone: up to and including the
+// kernel that tests the convergence of r_{k-1} (the rest, its tail, would
+// only find the solve done).
+enum Part { kWhole, kHead, kTail };
+
 // V-cycle of iteration k on b = r_k (finest), writing z = z_k.
 template <int DIM, typename T>
-static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg) {
+static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg, Part part = kWhole) {
   const Bnd &B = ws.bnd;
   const int nu = ws.nu;
   const SolverScalars *sc = ws.sc;
@@ -1499,6 +1521,7 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg) {
   for (int l = 0; l < ws.lc; ++l) {
     const Lay &L = ws.lev[l].lay, &Lc = ws.lev[l + 1].lay;
     T *xin = lev_xin<T>(ws, l, z);
+    if (l == 0 && part == kTail) continue;
     if (fused_level(ws, l)) {
       const void *b = l == 0 ? (k >= 1 ? (const void *)rprev : (const void *)r) : ws.lev[l].b;
       Down2DArgs<T> a = down_args<T>(ws, l, k, b, xin, cg.x, cg.pnew, cg.q, ws.r[k & 1]);
@@ -1506,6 +1529,7 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg) {
       const bool timed = l == 0 && timed_launch(ws, 0, e0, e1);
       launch_nu<T>(ws, l, nu, a, st, e0, e1);
       if (timed) ws.tk[ws.tcount++] = k;
+      if (part == kHead) return;
     } else if (fused3d(ws, l)) {
       Fused3DArgs<T> a = f3_args<T>(ws, l, l == 0 ? (const void *)r : ws.lev[l].b, l == 0);
       a.xout = xin;
@@ -1594,28 +1618,32 @@ static int np_rz_of(const PoissonWS &ws) {
 }
 
 template <int DIM, typename T>
-static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k) {
+static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k, Part part) {
   a.k = k;
   if (ws.cgcg) {
     // single-reduction CG: the update runs in the finest down kernel, or
     // in its own kernel when that level is not tiled
-    if (!fused_level(ws, 0)) {
+    const bool tiled = fused_level(ws, 0);
+    if (!tiled) {
       a.z = ws.z[0];
       a.pnew = ws.p[0];
       a.rold = ws.r[(k - 1) & 1];
       a.rnew = ws.r[k & 1];
       a.np_rz = np_rz_of(ws);
       hipEvent_t e0 = nullptr, e1 = nullptr;
-      const bool timed = timed_launch(ws, 2, e0, e1);
-      if (timed)
+      const bool timed = part != kTail && timed_launch(ws, 2, e0, e1);
+      if (part == kTail)
+        ;
+      else if (timed)
         hipExtLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, e0, e1, 0, a,
                               kRedBlocks, (const double *)ws.w, (const double *)ws.s[k & 1], ws.s[(k + 1) & 1]);
       else
         hipLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks,
                            (const double *)ws.w, (const double *)ws.s[k & 1], ws.s[(k + 1) & 1]);
       if (timed) ws.tk[ws.tcount++] = k;
+      if (part == kHead) return;
     }
-    vcycle<DIM, T>(st, ws, k, a);
+    vcycle<DIM, T>(st, ws, k, a, tiled ? part : kWhole);
     return;
   }
   // pq(k): p_k = z_{k-1} + beta p_{k-1}
@@ -1624,7 +1652,9 @@ static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k) {
   a.pnew = ws.p[k & 1];
   a.np_rz = np_rz_of(ws);
   a.flexible = !ws.cgcg;
-  hipLaunchKernelGGL((k_cg_pq<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks);
+  if (part != kTail)
+    hipLaunchKernelGGL((k_cg_pq<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks);
+  if (part == kHead) return;
   a.np_pq = kRedBlocks;
   if (!fused_level(ws, 0)) {
     a.rold = ws.r[(k - 1) & 1];
@@ -1634,12 +1664,35 @@ static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k) {
   vcycle<DIM, T>(st, ws, k, a);
 }
 
+// Waits for the scalars of the solve queued last, into ws.host_sc. The last
+// kernel writes them to pinned memory, which is watched for a while (the wait
+// ends some microseconds before a stream wait would); a solve that takes
+// longer, or a context without such memory, waits for the stream.
+static hipError_t await_scalars(hipStream_t st, PoissonWS &ws) {
+  if (!ws.host_out) {
+    const hipError_t e = hipMemcpyAsync(ws.host_sc, ws.sc, sizeof(SolverScalars), hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  }
+  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(200);
+  while (__atomic_load_n(&ws.host_out->seq, __ATOMIC_ACQUIRE) != ws.seq) {
+    for (int q = 0; q < 64; ++q) __builtin_ia32_pause();
+    if (std::chrono::steady_clock::now() > until) {
+      const hipError_t e = hipStreamSynchronize(st);
+      if (e != hipSuccess) return e;
+      if (__atomic_load_n(&ws.host_out->seq, __ATOMIC_ACQUIRE) != ws.seq) return hipErrorUnknown;
+    }
+  }
+  memcpy((void *)ws.host_sc, (const void *)&ws.host_out->sc, sizeof(SolverScalars));
+  return hipSuccess;
+}
+
 // The whole solve as one k_pcg_block launch (ws.block_pcg). With a log the
 // outcome is left on the device for the caller to read later; without one
 // this waits for it.
 template <int DIM, typename T>
 static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec, const double *x0, double rtol,
-                              int maxit, int *iters, double *relres, int *converged, SolveLog *log) {
+                              int maxit, int *iters, double *relres, int *converged, SolveLog *log,
+                              const std::function<hipError_t()> &after) {
   BlockPCGArgs<T> pa;
   pa.ca = coarse_args<T>(ws, ws.z[0], ws.r[0]);
   pa.L = ws.lay;
@@ -1662,15 +1715,17 @@ static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec,
   pa.cd = ws.ccd;
   pa.sc = ws.sc;
   pa.log = log;
+  pa.host = log ? nullptr : ws.host_out;
+  pa.seq = log ? 0 : ++ws.seq;
   ws.tol2 = pa.tol2;
   const bool plain = pa.ca.nq == 1;
   auto k = ws.vc ? (plain ? &k_pcg_block<DIM, T, true, true> : &k_pcg_block<DIM, T, true, false>)
                  : (plain ? &k_pcg_block<DIM, T, false, true> : &k_pcg_block<DIM, T, false, false>);
   hipLaunchKernelGGL(k, dim3(1), dim3(kBlkThreads<DIM>), 0, st, pa);
   hipError_t e = hipGetLastError();
+  if (e == hipSuccess && after) e = after();
   if (e != hipSuccess || log) return e;
-  e = hipMemcpyAsync(ws.host_sc, ws.sc, sizeof(SolverScalars), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  e = await_scalars(st, ws);
   if (e != hipSuccess) return e;
   const SolverScalars &h = *ws.host_sc;
   *iters = h.iters;
@@ -1681,8 +1736,9 @@ static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec,
 
 template <int DIM, typename T>
 static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, const double *x0, double rtol,
-                            int maxit, int expect, int *iters, double *relres, int *converged, SolveLog *log) {
-  if (ws.block_pcg) return solve_block<DIM, T>(st, ws, bvec, x0, rtol, maxit, iters, relres, converged, log);
+                            int maxit, int expect, int *iters, double *relres, int *converged, SolveLog *log,
+                            const std::function<hipError_t()> &after) {
+  if (ws.block_pcg) return solve_block<DIM, T>(st, ws, bvec, x0, rtol, maxit, iters, relres, converged, log, after);
   if (log) return hipErrorInvalidValue;
   CGArgs a;
   a.L = ws.lay;
@@ -1719,18 +1775,31 @@ static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, c
   hipLaunchKernelGGL(k_fold_partials, dim3(kRedBlocks), dim3(kBlock), 0, st, (const double *)ws.partials,
                      nblocks_for(ws.lay), ws.part_cc);
   vcycle<DIM, T>(st, ws, 0, a);
+  // Whole iterations up to the expected count (without one: about 0.7 per
+  // decade of the tolerance, what the V-cycle takes), then the head of the
+  // next, which finds whether they sufficed, and the work after the solve,
+  // gated on the outcome: the device goes on with it while the host reads the
+  // flag. Too few iterations cost an empty pass of the gated kernels; one
+  // iteration too many would cost its nine or more launches (2 us each).
   int k = 1;
-  int batch = expect > 0 ? expect + 1 : 4;
-  while (true) {
-    for (int q = 0; q < batch && k <= maxit + 1; ++q, ++k) iteration<DIM, T>(st, ws, a, k);
+  int batch = expect > 0 ? expect : std::max(2, (int)(-0.7 * std::log10(rtol) + 0.5));
+  for (int pass = 0;; ++pass) {
+    for (int q = 0; q < batch && k <= maxit; ++q, ++k) iteration<DIM, T>(st, ws, a, k, kWhole);
+    iteration<DIM, T>(st, ws, a, k, kHead);
+    // mean of the solution (the stored pressure is zero-mean)
+    hipLaunchKernelGGL((k_sum_x<DIM>), dim3(kRedBlocks), dim3(kBlock), 0, st, ws.lay, (const double *)ws.x,
+                       ws.partials, ws.met ? (const double *)ws.vol : (const double *)nullptr,
+                       (const SolverScalars *)ws.sc);
+    hipLaunchKernelGGL(k_fin_mean_x, dim3(1), dim3(kBlock), 0, st, (const double *)ws.partials, kRedBlocks,
+                       ws.met ? ws.volume : (double)ws.lay.ncells(), ws.sc, ws.host_out, ++ws.seq);
     e = hipGetLastError();
+    if (e == hipSuccess && after) e = after();
+    if (e == hipSuccess) e = await_scalars(st, ws);
     if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(ws.host_sc, ws.sc, sizeof(SolverScalars), hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
-    if (ws.host_sc->done || k > maxit + 1) break;
-    batch = 2;
+    if (ws.host_sc->done || k > maxit) break;
+    iteration<DIM, T>(st, ws, a, k, kTail);
+    ++k;
+    batch = std::min(pass, 2);
   }
   const SolverScalars &h = *ws.host_sc;
   *iters = h.iters;
@@ -1741,21 +1810,16 @@ static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, c
     if (ws.tk[q] < 2 || ws.tk[q] > h.iters) ws.tk[q] = -1;
   *relres = h.cc > 0 ? std::sqrt(h.rr / h.cc) : 0.0;
   *converged = h.done && !h.nonconv;
-  // mean of the solution (the stored pressure is zero-mean)
-  hipLaunchKernelGGL((k_sum_x<DIM>), dim3(kRedBlocks), dim3(kBlock), 0, st, ws.lay, (const double *)ws.x,
-                     ws.partials, ws.met ? (const double *)ws.vol : (const double *)nullptr);
-  hipLaunchKernelGGL(k_fin_mean_x, dim3(1), dim3(kBlock), 0, st, (const double *)ws.partials, kRedBlocks,
-                     ws.met ? ws.volume : (double)ws.lay.ncells(), ws.sc);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const double *x0, double rtol,
-                         int maxit, int expect_iters, int *iters, double *relres, int *converged, SolveLog *log) {
-  if (ws.lay.ndim == 3)
-    return ws.mixed ? solve_dim<3, float>(st, ws, b, x0, rtol, maxit, expect_iters, iters, relres, converged, log)
-                    : solve_dim<3, double>(st, ws, b, x0, rtol, maxit, expect_iters, iters, relres, converged, log);
-  return ws.mixed ? solve_dim<2, float>(st, ws, b, x0, rtol, maxit, expect_iters, iters, relres, converged, log)
-                  : solve_dim<2, double>(st, ws, b, x0, rtol, maxit, expect_iters, iters, relres, converged, log);
+                         int maxit, int expect_iters, int *iters, double *relres, int *converged, SolveLog *log,
+                         const std::function<hipError_t()> &after) {
+  const bool three = ws.lay.ndim == 3;
+  auto solve = ws.mixed ? (three ? &solve_dim<3, float> : &solve_dim<2, float>)
+                        : (three ? &solve_dim<3, double> : &solve_dim<2, double>);
+  return solve(st, ws, b, x0, rtol, maxit, expect_iters, iters, relres, converged, log, after);
 }
 
 // ---------------------------------------------------------------------------
