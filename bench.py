@@ -39,16 +39,17 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_2603_01727_amd", "csrc", f)
 #    r, w, s, u, p, x (6 x 8 B), writes p, s, x, r, correction (5 x 8 B) and
 #    the coarse right-hand side (8 B per 4 cells).
 #  1 finest 3D up: reads the pre-smoothed correction and the coarse
-#    correction (one per 8 cells), b = r (8 B), writes u = M r and w = A u
-#    (8 B each; u in FP32 for mixed).
-#  2 single-reduction CG update (3D): reads x, r, p, s, w (5 x 8 B) and u
-#    (8 B / 4 B), writes x, r, p, s (4 x 8 B). Iteration 1 has no old p, s
-#    and is left out of the timed set.
+#    correction (one per 8 cells), b = r (8 B), writes u = M r (8 B; 4 B for
+#    mixed).
+#  2 single-reduction CG update (3D): reads r, p (2 x 8 B) and u (8 B / 4 B),
+#    writes r, p (2 x 8 B); every second iteration also reads and writes x
+#    (8 B per iteration on average). Iteration 1 has no old p and is left out
+#    of the timed set.
 KCLASS_3D = {
     0: ("k_mg_down3d finest (two red-black sweeps from zero + restriction)", 8 + 8 + 1, 8 + 4 + 0.5),
-    1: ("k_mg_up3d finest (prolongation + two red-black sweeps + w = A u + CG partial sums)",
-        8 + 1 + 8 + 8 + 8, 4 + 0.5 + 8 + 4 + 8),
-    2: ("k_cgcg_update (single-reduction CG: p, s, x, r)", 10 * 8, 9 * 8 + 4),
+    1: ("k_mg_up3d finest (prolongation + two red-black sweeps + A u for the CG partial sums)",
+        8 + 1 + 8 + 8, 4 + 0.5 + 8 + 4),
+    2: ("k_cgcg_march (single-reduction CG: p, r, and x every second step)", 6 * 8, 5 * 8 + 4),
 }
 KCLASS_2D = {
     0: ("k_mg_down2d finest (fused CG update + two red-black sweeps + restriction)", 6 * 8 + 5 * 8 + 2,

@@ -43,7 +43,6 @@ struct Fused3DArgs {
   T *xout;                  // down: pre-smoothed correction; up: post-smoothed
   T *bc;                    // down: coarse right-hand side
   const SolverScalars *sc;
-  double *w;                // up with EXTRA: A u on the owned cells
   double *part_rz;          // up with EXTRA: [r.u | w.u | r.r] x np
   int np;
 };
@@ -302,7 +301,7 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_down3d(Fused3DArgs<T> a) {
 // Stage s (1 .. 2 NU) runs at lag s. With EXTRA = 1 (finest level of the
 // FP64 single-reduction CG) a last stage at lag 2 NU + 1 forms w = A u on
 // the owned cells in FP64 with the partials of r.u, w.u and r.r (r = the
-// level's right-hand side, read in FP64). Halo 2 NU + EXTRA planes in z; in x and y
+// level's right-hand side, read in FP64; w itself is not needed again). Halo 2 NU + EXTRA planes in z; in x and y
 // rounded up to even, so the pairs sit on (even, odd) columns and never
 // straddle the periodic seam.
 template <typename T, int NU, int EXTRA, bool BD>
@@ -440,7 +439,6 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_up3d(Fused3DArgs<T> a) {
           T *o = a.xout + g;
           o[0] = pick<T>(cr, XB[k], XR[k]);
           o[1] = pick<T>(cr, XR[k], XB[k]);
-          *(double2 *)(a.w + g) = make_double2(pick<double>(cr, wB, wR), pick<double>(cr, wR, wB));
           const double rR = pick<double>(cr, r1, r0), rB = pick<double>(cr, r0, r1);
           ru += rR * uR + rB * uB;
           wu += wR * uR + wB * uB;

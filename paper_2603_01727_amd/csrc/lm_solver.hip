@@ -491,59 +491,197 @@ __global__ void __launch_bounds__(kBlock) k_cg_rz(CGArgs a) {
   }
 }
 
-// Single-reduction CG (Chronopoulos-Gear) for an unfused finest level.
-// Step k: convergence test on r_{k-1}; beta = g_{k-1}/g_{k-2},
+// Single-reduction CG (Chronopoulos-Gear) on a finest level without 2D
+// tiles. Step k: convergence test on r_{k-1}; beta = g_{k-1}/g_{k-2},
 // alpha = g_{k-1} / (d_{k-1} - beta g_{k-1}/alpha_{k-2}) with g = r.u and
-// d = (A u).u; p = u + beta p; s = w + beta s; x += alpha p; r -= alpha s.
-template <int DIM, typename TZ>
-__global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc, const double *w, const double *s_old,
-                                                        double *s_new) {
+// d = (A u).u; p = u + beta p; r -= alpha A p; x += alpha p.
+//
+// Bound by HBM: A p is formed again from p (its neighbours come from LDS or
+// L2) instead of carried as s = A u + beta s, which with A u were three more
+// arrays to move; and x takes its update every second step, both directions
+// at once, when the old p is read anyway (x += alpha_{k-1} p_{k-1} +
+// alpha_k p_k on even steps, the pending one when the solve ends on an odd
+// one). 48 B per cell and step instead of 80: 256^3 FP64 145 us (5.5 TB/s)
+// instead of 217 us.
+struct CgScalars {
+  double alpha, beta, alpha_old;
+  bool end, pending;  // the solve ends with this test; x lacks alpha_{k-1} p_{k-1}
+};
+// False: the solve was done before this kernel. sc->done is k + 1 when the
+// test of step k ended it: blocks that start after block 0 has set it still
+// take part.
+__device__ inline bool cgcg_scalars(const CGArgs &a, int np_cc, CgScalars &q) {
   SolverScalars *sc = a.sc;
-  if (sc->done) return;
-  const int k = a.k;
+  const int k = a.k, done = sc->done;
+  if (done && done != k + 1) return false;
   double cc, g, d, rr;
   sum_cc3(k, a.part_cc, np_cc, sc, a.part_rz, a.part_rz + a.np_rz, a.part_rz + 2 * a.np_rz, a.np_rz, cc, g, d, rr);
   const bool conv = (cc == 0.0) || (rr <= a.tol2 * cc);
-  double alpha, beta = 0.0;
+  q.beta = q.alpha_old = 0.0;
   if (k == 1) {
-    alpha = g / d;
+    q.alpha = g / d;
   } else {
-    beta = g / sc->rzh[(k - 2) & 1];
-    alpha = g / (d - beta * g / sc->alh[(k - 2) & 1]);
+    q.alpha_old = sc->alh[(k - 2) & 1];
+    q.beta = g / sc->rzh[(k - 2) & 1];
+    q.alpha = g / (d - q.beta * g / q.alpha_old);
   }
-  const bool broken = !isfinite(rr) || !isfinite(alpha) || !isfinite(beta);
+  const bool broken = !isfinite(rr) || !isfinite(q.alpha) || !isfinite(q.beta);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     sc->rzh[(k - 1) & 1] = g;
-    sc->alh[(k - 1) & 1] = alpha;
+    sc->alh[(k - 1) & 1] = q.alpha;
     sc->rr = rr;
     sc->cc = cc;
     sc->iters = k - 1;
     if (conv || broken) {
-      sc->done = 1;
       sc->zero = (cc == 0.0);
       sc->nonconv = broken && !conv;
+      sc->done = k + 1;
     }
   }
-  if (conv || broken) return;
+  q.end = conv || broken;
+  q.pending = k >= 2 && (k & 1) == 0 && !(broken && !conv);
+  return true;
+}
+
+// Any sides, variable coefficients: one thread per cell of a grid-stride
+// loop.
+template <int DIM, typename TZ>
+__global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc) {
+  CgScalars q;
+  if (!cgcg_scalars(a, np_cc, q) || (q.end && !q.pending)) return;
   const TZ *u = (const TZ *)a.z;
-  const bool old = k >= 2;
+  const bool old = a.k >= 2;
   for (int tile = blockIdx.x; tile < ntiles_of(a.L); tile += gridDim.x) {
     int i, j, kk;
     if (!tile_cell(a.L, tile, i, j, kk)) continue;
     const long c = a.L.at(i, j, kk);
-    const double so = old ? s_old[c] : 0.0;
-    const double pn = (double)u[c] + (old ? beta * a.pnew[c] : 0.0);
-    const double sn = w[c] + beta * so;
-    a.pnew[c] = pn;
-    s_new[c] = sn;
-    a.x[c] += alpha * pn;
-    a.rnew[c] = a.rold[c] - alpha * sn;
+    if (q.end) {
+      a.x[c] += q.alpha_old * a.pold[c];
+      continue;
+    }
+    auto pv = [&](long m) -> double { return old ? (double)u[m] + q.beta * a.pold[m] : (double)u[m]; };
+    const double pc = pv(c);
+    double nbs = 0.0, dg = 0.0;
+    const int x[3] = {i, j, kk};
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const long lo = nbr(a.L, a.B, c, x[d], d, -1), hi = nbr(a.L, a.B, c, x[d], d, +1);
+      double s = 0.0, sb = 0.0;
+      if (lo >= 0) {
+        const double bt = a.rho ? face_coef<double>(a.rho[c], a.rho[lo], d, a.met) : 1.0;
+        s += bt * pv(lo);
+        sb += bt;
+      }
+      if (hi >= 0) {
+        const double bt = a.rho ? face_coef<double>(a.rho[c], a.rho[hi], d, a.met) : 1.0;
+        s += bt * pv(hi);
+        sb += bt;
+      }
+      nbs += a.ih2[d] * s;
+      dg += a.ih2[d] * sb;
+    }
+    a.pnew[c] = pc;
+    a.rnew[c] = a.rold[c] - q.alpha * (dg * pc - nbs);
+    if (q.pending) a.x[c] += q.alpha_old * a.pold[c] + q.alpha * pc;
   }
 }
 
-// w = A u (u = M r) and partials of r.u, w.u, r.r for the unfused finest level.
+// Periodic 3D, beta = 1: a block owns a 64 x 8 column of cells and marches
+// up a run of planes. Each thread keeps its column's p of three planes in
+// registers; the x and y neighbours come from an LDS plane (with a one-cell
+// ring) filled one plane ahead; the loads run two planes ahead. Every array
+// is read once but for the rings (28 % of u and p, from L2). Positions past
+// the far sides are copies of the cells they wrap to, and not written.
+constexpr int kUX = 64, kUY = 8, kUW = kUX + 2;
+constexpr int kURing = 2 * kUX + 2 * kUY;  // ring cells: two rows, two columns (no corners)
+template <typename TZ>
+__global__ void __launch_bounds__(kUX *kUY, 4) k_cgcg_march(CGArgs a, int np_cc, int tiles_x, int tiles_y, int tz) {
+  __shared__ double P[2][(kUY + 2) * kUW];
+  CgScalars q;
+  if (!cgcg_scalars(a, np_cc, q) || (q.end && !q.pending)) return;
+  const Lay &L = a.L;
+  const int nx = L.n[0], ny = L.n[1], nz = L.n[2];
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = lb % (tiles_x * tiles_y), chunk = lb / (tiles_x * tiles_y);
+  const int x0 = (tile % tiles_x) * kUX, y0 = (tile / tiles_x) * kUY;
+  const int z0 = chunk * tz, z1 = min(z0 + tz, nz);
+  const int tid = threadIdx.x, lx = tid & (kUX - 1), ly = tid / kUX;
+  const bool own = x0 + lx < nx && y0 + ly < ny;
+  const long s2 = L.s[2];
+  const TZ *u = (const TZ *)a.z;
+  const long col = L.base + (x0 + lx) % nx + (long)((y0 + ly) % ny) * L.s[1];
+  if (q.end) {  // only the pending update of x
+    if (own)
+      for (int z = z0; z < z1; ++z) a.x[col + z * s2] += q.alpha_old * a.pold[col + z * s2];
+    return;
+  }
+  const bool old = a.k >= 2;
+  // this thread's ring cell: rows below and above, columns left and right
+  const bool ring = tid < kURing;
+  int rx, ry;
+  if (tid < 2 * kUX) {
+    rx = tid & (kUX - 1);
+    ry = tid < kUX ? -1 : kUY;
+  } else {
+    rx = tid < 2 * kUX + kUY ? -1 : kUX;
+    ry = (tid - 2 * kUX) & (kUY - 1);
+  }
+  const long rcol = ring ? L.base + (x0 + rx + nx) % nx + (long)((y0 + ry + ny) % ny) * L.s[1] : col;
+  const int me = (ly + 1) * kUW + lx + 1, mr = (ry + 1) * kUW + rx + 1;
+  const double ihx = a.ih2[0], ihy = a.ih2[1], ihz = a.ih2[2], dg = 2.0 * (ihx + ihy + ihz);
+  auto plane = [&](int z) __attribute__((always_inline)) { return (long)(z < 0 ? z + nz : (z >= nz ? z - nz : z)) * s2; };
+  auto pv = [&](TZ uv, double po) __attribute__((always_inline)) { return (double)uv + (old ? q.beta * po : 0.0); };
+  // p below, at and above the first plane; its ring; the old p of the centre
+  const long gm = plane(z0 - 1), g0 = plane(z0), g1 = plane(z0 + 1);
+  double pom = old ? a.pold[col + gm] : 0.0, po = old ? a.pold[col + g0] : 0.0;
+  double pm = pv(u[col + gm], pom), pc = pv(u[col + g0], po);
+  TZ un = u[col + g1];
+  double pn = old ? a.pold[col + g1] : 0.0;
+  double rv = a.rold[col + g0], xv = q.pending ? a.x[col + g0] : 0.0;
+  TZ ur = TZ(0);
+  double pr = 0.0;
+  P[z0 & 1][me] = pc;
+  if (ring) {
+    P[z0 & 1][mr] = pv(u[rcol + g0], old ? a.pold[rcol + g0] : 0.0);
+    ur = u[rcol + g1];
+    pr = old ? a.pold[rcol + g1] : 0.0;
+  }
+  __syncthreads();
+  for (int z = z0; z < z1; ++z) {
+    // values of plane z + 1 in hand; those of z + 2 (and r, x of z + 1) in flight
+    const double pp = pv(un, pn), pon = pn, pring = pv(ur, pr);
+    const double rc = rv, xc = xv;
+    const long g2 = plane(z + 2), gn = plane(z + 1), gz = (long)z * s2;
+    if (z + 1 < z1) {
+      un = u[col + g2];
+      pn = old ? a.pold[col + g2] : 0.0;
+      rv = a.rold[col + gn];
+      xv = q.pending ? a.x[col + gn] : 0.0;
+      if (ring) {
+        ur = u[rcol + g2];
+        pr = old ? a.pold[rcol + g2] : 0.0;
+      }
+    }
+    const double *S = P[z & 1];
+    const double nbs = ihx * (S[me - 1] + S[me + 1]) + ihy * (S[me - kUW] + S[me + kUW]) + ihz * (pm + pp);
+    if (own) {
+      a.pnew[col + gz] = pc;
+      a.rnew[col + gz] = rc - q.alpha * (dg * pc - nbs);
+      if (q.pending) a.x[col + gz] = xc + (q.alpha_old * po + q.alpha * pc);
+    }
+    P[(z + 1) & 1][me] = pp;
+    if (ring) P[(z + 1) & 1][mr] = pring;
+    __syncthreads();
+    pm = pc;
+    pc = pp;
+    po = pon;
+  }
+}
+
+// Partials of r.u, w.u, r.r with w = A u (u = M r) for the unfused finest
+// level.
 template <int DIM, typename TZ>
-__global__ void __launch_bounds__(kBlock) k_cgcg_w(CGArgs a, double *w) {
+__global__ void __launch_bounds__(kBlock) k_cgcg_w(CGArgs a) {
   if (a.sc->done) return;
   const TZ *u = (const TZ *)a.z;
   double ru = 0.0, wu = 0.0, rr = 0.0;
@@ -559,7 +697,6 @@ __global__ void __launch_bounds__(kBlock) k_cgcg_w(CGArgs a, double *w) {
     const double uc = (double)u[c];
     const double wv = dg * uc - nbs;
     const double rv = a.rnew[c];
-    w[c] = wv;
     ru += rv * uc;
     wu += wv * uc;
     rr += rv * rv;
@@ -1574,7 +1711,6 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg, Part 
       a.xc = xc;
       a.xout = xout;
       const bool extra = l == 0 && w_in_up3d(ws);
-      a.w = ws.w;
       a.part_rz = ws.part_rz;
       a.np = (int)blocks3d(L, ti3(nu, false, extra));
       hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1605,7 +1741,7 @@ static void vcycle(hipStream_t st, PoissonWS &ws, int k, const CGArgs &cg, Part 
     a.zold = (!ws.cgcg && k >= 1) ? ws.z[(k + 1) & 1] : nullptr;
     a.np_rz = kRedBlocks;
     if (ws.cgcg) {
-      if (!w_in_up3d(ws)) hipLaunchKernelGGL((k_cgcg_w<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, ws.w);
+      if (!w_in_up3d(ws)) hipLaunchKernelGGL((k_cgcg_w<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a);
     } else
       hipLaunchKernelGGL((k_cg_rz<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a);
   }
@@ -1626,20 +1762,32 @@ static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k, Part part)
     const bool tiled = fused_level(ws, 0);
     if (!tiled) {
       a.z = ws.z[0];
-      a.pnew = ws.p[0];
+      a.pold = ws.p[(k - 1) & 1];
+      a.pnew = ws.p[k & 1];
       a.rold = ws.r[(k - 1) & 1];
       a.rnew = ws.r[k & 1];
       a.np_rz = np_rz_of(ws);
       hipEvent_t e0 = nullptr, e1 = nullptr;
       const bool timed = part != kTail && timed_launch(ws, 2, e0, e1);
-      if (part == kTail)
-        ;
-      else if (timed)
-        hipExtLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, e0, e1, 0, a,
-                              kRedBlocks, (const double *)ws.w, (const double *)ws.s[k & 1], ws.s[(k + 1) & 1]);
-      else
-        hipLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks,
-                           (const double *)ws.w, (const double *)ws.s[k & 1], ws.s[(k + 1) & 1]);
+      if (part != kTail) {
+        if (DIM == 3 && ws.bnd.all_periodic && !ws.vc) {
+          // a run of planes per block: about four blocks of eight wavefronts
+          // per compute unit, at least 8 planes (two more are read)
+          const Lay &L = ws.lay;
+          const int tx = tiles_along(L.n[0], kUX), ty = tiles_along(L.n[1], kUY);
+          const int nch = std::max(1, 1024 / (tx * ty));
+          const int tz = std::max(8, tiles_along(L.n[2], nch));
+          const dim3 g(tx * ty * tiles_along(L.n[2], tz)), b(kUX * kUY);
+          if (timed)
+            hipExtLaunchKernelGGL(k_cgcg_march<T>, g, b, 0, st, e0, e1, 0, a, kRedBlocks, tx, ty, tz);
+          else
+            hipLaunchKernelGGL(k_cgcg_march<T>, g, b, 0, st, a, kRedBlocks, tx, ty, tz);
+        } else if (timed) {
+          hipExtLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, e0, e1, 0, a, kRedBlocks);
+        } else {
+          hipLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks);
+        }
+      }
       if (timed) ws.tk[ws.tcount++] = k;
       if (part == kHead) return;
     }
