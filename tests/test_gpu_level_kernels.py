@@ -116,3 +116,14 @@ def test_tiles_stretched(n, precision):
 @pytest.mark.parametrize("n", [(40, 24, 28), (8, 48, 16), (8, 8, 80), (12, 20, 24), (32, 40, 36), (32, 40, 8)], ids=str)
 def test_fused_3d_levels(n, nu, precision):
     _check(n, None, precision, nu=nu)
+
+
+# 3D CG update beyond the one-workgroup solve: periodic columns that do not
+# divide the grid in x or y, and the form for other sides; the coarsest
+# levels hold 540, 480 and 204 cells (dense inverse read in long and short
+# runs)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("bc", [None, WALLS, OPEN], ids=["periodic", "walls", "open"])
+@pytest.mark.parametrize("n", [(72, 20, 24), (24, 20, 32), (136, 12, 16)], ids=str)
+def test_cg_update_3d(n, bc, precision):
+    _check(n, bc, precision)
