@@ -11,11 +11,12 @@
 //   Adams steps  AB2 predictor / AM2 corrector                          (Eq 3.1-3.18)
 //   residuals    R_H, R_v of Eq 3.4, 3.8, 3.26 with tau of Eq 2.46 and the
 //                penalisation terms of Eq 3.30-3.32.
-// The residual transpose is a gather: for every input cell m the residuals
-// of the 3^DIM cells whose stencils reach m are re-evaluated with dual
-// numbers seeded at m (derivatives with respect to H, the DIM velocity
-// components and the DIM face fluxes at m) and contracted with the residual
-// cotangents. No atomics; deterministic.
+// The residual transpose is a gather. Away from sides it is written out face
+// by face (k_adj_resid_in); in the band along sides, for every input cell m
+// the residuals of the 3^DIM cells whose stencils reach m are re-evaluated
+// with dual numbers seeded at m (derivatives with respect to H, the DIM
+// velocity components and the DIM face fluxes at m) and contracted with the
+// residual cotangents. No atomics; deterministic.
 #include <type_traits>
 
 #include "lm_device.h"
@@ -135,15 +136,6 @@ __device__ inline Dual<N> dpow(const Dual<N> &x, double p) {
 template <int DIM, int R>
 using DD = Dual<1 + R + 2 * DIM>;
 
-// f(integral_constant<int, I>) for I = B .. E-1, unrolled at compile time.
-template <int B, int E, typename F>
-__device__ __attribute__((always_inline)) inline void adj_static_for(F &&f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>());
-    adj_static_for<B + 1, E>(f);
-  }
-}
-
 struct Ix {
   int i, j, k;
 };
@@ -166,14 +158,13 @@ __device__ inline long pw(const Lay &L, Ix x) {
 
 // Loader of the level fields at cell positions, interior or ghost; values
 // at cell m carry unit seeds: H -> 0, Z -> 1 (R = 1), v_c -> 1 + R + c,
-// F_d -> 1 + R + DIM + d. W = 0: every direction periodic (positions wrap);
-// W = 1: slip / no-slip wall sides as well, whose ghost values follow the
-// forward ghost rules (mirror, or 2 x side value - mirror; corner ghosts by
+// F_d -> 1 + R + DIM + d. Ghost values beyond a wall follow the forward
+// ghost rules (mirror, or 2 x side value - mirror; corner ghosts by
 // the rules of the highest out-of-range direction first), so that a ghost
 // carries the seed of the interior cell it mirrors with weight -1 or +1.
 // The body mask and targets are constants (null: no body, or a zero
 // target).
-template <int DIM, int R, int W>
+template <int DIM, int R>
 struct Loader {
   Lay L;
   Bnd B;
@@ -183,11 +174,8 @@ struct Loader {
   const unsigned char *chi;
   const double *H_ib, *Z_ib, *v_ib[3];
   Ix m;
-  // cell constants at x (x wrapped into a periodic grid first)
-  __device__ long cidx(Ix x) const {
-    if (!W) x = wrap(L, x);
-    return L.at(x.i, x.j, x.k);
-  }
+  // cell constants at x
+  __device__ long cidx(Ix x) const { return L.at(x.i, x.j, x.k); }
   __device__ double chi_at(Ix x) const { return chi ? (double)chi[cidx(x)] : 0.0; }
   __device__ double hib(Ix x) const { return H_ib ? H_ib[cidx(x)] : 0.0; }
   __device__ double zib(Ix x) const { return Z_ib ? Z_ib[cidx(x)] : 0.0; }
@@ -197,16 +185,6 @@ struct Loader {
   // of the three cells inside; with at most one outflow direction (checked
   // at set-up) a ghost spans at most three cells.
   __device__ DD<DIM, R> load(const double *a, int f, Ix x, int seed) const {
-    if (!W) {
-      // periodic: the seed test on unwrapped coordinates (exact when every
-      // direction has at least 3 cells, as readers lie within 2 of m), which
-      // an unrolled gather resolves at compile time
-      const bool seeded = x.i == m.i && x.j == m.j && x.k == m.k;
-      x = wrap(L, x);
-      DD<DIM, R> r(a[L.at(x.i, x.j, x.k)]);
-      if (seeded) r.d[seed] = 1.0;
-      return r;
-    }
     int pos[3][3] = {{x.i, x.j, x.k}, {0, 0, 0}, {0, 0, 0}};
     double w[3] = {1.0, 0.0, 0.0};
     int nt = 1;
@@ -261,7 +239,6 @@ struct Loader {
   // flux on the +d face of x (x interior, or one cell below the low side
   // along d: that side's face, a constant on a wall)
   __device__ DD<DIM, R> ff(int d, Ix x) const {
-    if (!W) return load(F[d], 0, x, 1 + R + DIM + d);
     int pos[3] = {x.i, x.j, x.k};
     if (pos[d] < 0 && B.periodic[d]) pos[d] += L.n[d];
     DD<DIM, R> r(F[d][L.at(pos[0], pos[1], pos[2])]);
@@ -305,8 +282,8 @@ __device__ inline Dual<N> theta_dual(const AdjPhys &P, const Dual<N> &Z) {
 }
 
 // T(Z, H) of Eq 3.42; without reaction T = qs (H - 1).
-template <int DIM, int R, int W>
-__device__ inline DD<DIM, R> temp_at(const AdjPhys &P, const Loader<DIM, R, W> &ld, Ix x) {
+template <int DIM, int R>
+__device__ inline DD<DIM, R> temp_at(const AdjPhys &P, const Loader<DIM, R> &ld, Ix x) {
   if (R) return P.qs * (ftilde_dual(P, ld.zz(x)) + ld.hh(x));
   return P.qs * (ld.hh(x) - 1.0);
 }
@@ -327,17 +304,16 @@ __device__ inline Dual<N> kappa_dual(const AdjPhys &P, const Dual<N> &T) {
   return dpow(T, P.sigma);
 }
 
-// Conductivity at a cell position. Ghosts (W = 1) follow the forward ghost
+// Conductivity at a cell position. Ghosts follow the forward ghost
 // fill: at an isothermal wall 2 kappa(T_w) - kappa(T) of the interior cell
 // the ghost position clamps to; elsewhere kappa of the ghost temperature,
 // with the ghost Z clamped to [0, S+1].
-template <int DIM, int R, int W>
-__device__ inline DD<DIM, R> kap_at(const AdjPhys &P, const Loader<DIM, R, W> &ld, Ix x) {
-  if (!W || ld.inside(x)) {
+template <int DIM, int R>
+__device__ inline DD<DIM, R> kap_at(const AdjPhys &P, const Loader<DIM, R> &ld, Ix x) {
+  if (ld.inside(x)) {
     // kappa of a cell from the level's precomputed kappa and d kappa/dT:
     // T = qs (F~(Z) + H) carries the seeds (dT/dH = qs, dT/dZ = qs F~'(Z))
     const bool seeded = x.i == ld.m.i && x.j == ld.m.j && x.k == ld.m.k;
-    if (!W) x = wrap(ld.L, x);
     const long c = ld.L.at(x.i, x.j, x.k);
     DD<DIM, R> r(ld.kap[c]);
     if (seeded) {
@@ -365,8 +341,8 @@ __device__ inline DD<DIM, R> kap_at(const AdjPhys &P, const Loader<DIM, R, W> &l
 // tau_{d c} for every component c on the face between cell x and its +d
 // neighbour (Eq 2.46 on d-faces): normal derivatives across the face,
 // tangential ones as the mean of the centred differences of the two cells.
-template <int DIM, int R, int W>
-__device__ inline void tau_face(const AdjPhys &P, const Loader<DIM, R, W> &ld, Ix x, int d, DD<DIM, R> tau[DIM]) {
+template <int DIM, int R>
+__device__ inline void tau_face(const AdjPhys &P, const Loader<DIM, R> &ld, Ix x, int d, DD<DIM, R> tau[DIM]) {
   const Ix y = off(x, d, 1);
   const DD<DIM, R> kf = 0.5 * (kap_at(P, ld, x) + kap_at(P, ld, y));
   DD<DIM, R> D[DIM][DIM];  // D[k][c] = d v_c / d x_k on the face
@@ -398,8 +374,8 @@ __device__ inline void tau_face(const AdjPhys &P, const Loader<DIM, R, W> &ld, I
 // Advection (face fluxes times the one-sided differences, averaged to the
 // centre) and centred diffusion of a scalar at cell x (Eq 3.26b, section
 // 3.2): field 0 H, 1 Z.
-template <int DIM, int R, int W>
-__device__ inline void scalar_dual(const AdjPhys &P, const Loader<DIM, R, W> &ld, Ix x, int f, const DD<DIM, R> &kc,
+template <int DIM, int R>
+__device__ inline void scalar_dual(const AdjPhys &P, const Loader<DIM, R> &ld, Ix x, int f, const DD<DIM, R> &kc,
                                    DD<DIM, R> &adv, DD<DIM, R> &dif) {
   auto val = [&](Ix y) { return f == 0 ? ld.hh(y) : ld.zz(y); };
   const DD<DIM, R> sc = val(x);
@@ -421,8 +397,8 @@ __device__ inline void scalar_dual(const AdjPhys &P, const Loader<DIM, R, W> &ld
 // arithmetic of the forward residual (Eq 3.2a, 3.4a, 3.8a with the flux
 // forms of Eq 3.26, the Lewis-number factors of Eq 3.35), with the
 // penalisation of the body mask chi (Eq 3.30-3.32).
-template <int DIM, int R, int W>
-__device__ inline void resid_cell(const AdjPhys &P, const Loader<DIM, R, W> &ld, Ix x, DD<DIM, R> &RH,
+template <int DIM, int R>
+__device__ inline void resid_cell(const AdjPhys &P, const Loader<DIM, R> &ld, Ix x, DD<DIM, R> &RH,
                                   DD<DIM, R> &RZ, DD<DIM, R> Rv[DIM]) {
   const DD<DIM, R> Hc = ld.hh(x);
   const DD<DIM, R> Tc = temp_at(P, ld, x);
@@ -452,8 +428,8 @@ __device__ inline void resid_cell(const AdjPhys &P, const Loader<DIM, R, W> &ld,
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
     DD<DIM, R> tp[DIM], tm[DIM];
-    tau_face<DIM, R, W>(P, ld, x, d, tp);
-    tau_face<DIM, R, W>(P, ld, off(x, d, -1), d, tm);
+    tau_face<DIM, R>(P, ld, x, d, tp);
+    tau_face<DIM, R>(P, ld, off(x, d, -1), d, tm);
 #pragma unroll
     for (int c = 0; c < DIM; ++c) visc[c] = visc[c] + (tp[c] - tm[c]) / P.h[d];
   }
@@ -526,23 +502,23 @@ hipError_t launch_adj_kappa(hipStream_t st, const AdjCellArgs &a) {
   return hipGetLastError();
 }
 
-// (Hb, Zb, vb, Fb) += (dR/d(H, Z, v, F))^T (RbH, RbZ, Rbv) by gather over
-// the 3^DIM cells whose residual stencils reach the cell (with wall or
-// inflow sides, the interior ones: a ghost mirrors a cell within one cell
-// of the reader; towards a high outflow side two cells further, as its
-// extrapolated ghost reads three cells in). The flux of a wall or inflow
+// (Hb, Zb, vb, Fb) += (dR/d(H, Z, v, F))^T (RbH, RbZ, Rbv) along wall, inflow
+// and outflow sides, by gather over the 3^DIM interior cells whose residual
+// stencils reach the cell (a ghost mirrors a cell within one cell of the
+// reader; towards a high outflow side two cells further, as its extrapolated
+// ghost reads three cells in). The flux of a wall or inflow
 // face is a constant of the step: its cotangent stays 0.
-template <int DIM, int R, int W>
+template <int DIM, int R>
 __global__ void __launch_bounds__(kBlock) k_adj_resid(AdjResidArgs a) {
   constexpr int N = 1 + R + 2 * DIM;
   CellPos p;
   if (!cell_of_thread(a.L, p)) return;
-  if (a.box_mode) {
+  if (a.box_mode) {  // the cells outside the box
     const bool in = p.i >= a.box_lo[0] && p.i <= a.box_hi[0] && p.j >= a.box_lo[1] && p.j <= a.box_hi[1] &&
                     p.k >= a.box_lo[2] && p.k <= a.box_hi[2];
-    if (in != (a.box_mode == 1)) return;
+    if (in) return;
   }
-  Loader<DIM, R, W> ld;
+  Loader<DIM, R> ld;
   ld.L = a.L;
   ld.B = a.B;
   ld.sd = a.sd;
@@ -568,15 +544,13 @@ __global__ void __launch_bounds__(kBlock) k_adj_resid(AdjResidArgs a) {
   // two cells towards a high outflow side
   const int pm[3] = {p.i, p.j, p.k};
   int hi[3] = {1, 1, kr};
-  if (W)
 #pragma unroll
-    for (int d = 0; d < DIM; ++d)
-      if (a.B.kind[d][1] == LM_SIDE_OUTFLOW && pm[d] == a.L.n[d] - 3) hi[d] = 2;
-  // the residual of cell x (unwrapped in a periodic grid) contracted with
-  // its cotangents into acc
+  for (int d = 0; d < DIM; ++d)
+    if (a.B.kind[d][1] == LM_SIDE_OUTFLOW && pm[d] == a.L.n[d] - 3) hi[d] = 2;
+  // the residual of cell x contracted with its cotangents into acc
   auto gather = [&](Ix x) __attribute__((always_inline)) {
     DD<DIM, R> RH, RZ, Rv[DIM];
-    resid_cell<DIM, R, W>(a.P, ld, x, RH, RZ, Rv);
+    resid_cell<DIM, R>(a.P, ld, x, RH, RZ, Rv);
     const long c = ld.cidx(x);
     const double rh = a.RbH[c], rz = R ? a.RbZ[c] : 0.0;
     double r[DIM];
@@ -591,30 +565,19 @@ __global__ void __launch_bounds__(kBlock) k_adj_resid(AdjResidArgs a) {
       acc[q] += s;
     }
   };
-  if constexpr (!W) {
-    // periodic: the 3^DIM offsets unrolled, so that every seed test (which
-    // stencil position is cell m) is a constant and the derivative
-    // arithmetic of the positions that are not m folds away
-    adj_static_for<0, (DIM == 3 ? 27 : 9)>([&](auto T) __attribute__((always_inline)) {
-      constexpr int t = decltype(T)::value;
-      constexpr int di = t % 3 - 1, dj = (t / 3) % 3 - 1, dk = DIM == 3 ? t / 9 - 1 : 0;
-      gather(Ix{p.i + di, p.j + dj, p.k + dk});
-    });
-  } else {
-    for (int dk = -kr; dk <= hi[2]; ++dk)
-      for (int dj = -1; dj <= hi[1]; ++dj)
-        for (int di = -1; di <= hi[0]; ++di) {
-          Ix x{p.i + di, p.j + dj, p.k + dk};
-          if (!ld.inside(x)) {
-            const int q[3] = {x.i, x.j, x.k};
-            bool wall = false;
-            for (int d = 0; d < DIM; ++d)
-              if ((q[d] < 0 || q[d] >= a.L.n[d]) && !a.B.periodic[d]) wall = true;
-            if (wall) continue;  // a ghost has no residual
-          }
-          gather(wrap(a.L, x));
+  for (int dk = -kr; dk <= hi[2]; ++dk)
+    for (int dj = -1; dj <= hi[1]; ++dj)
+      for (int di = -1; di <= hi[0]; ++di) {
+        Ix x{p.i + di, p.j + dj, p.k + dk};
+        if (!ld.inside(x)) {
+          const int q[3] = {x.i, x.j, x.k};
+          bool wall = false;
+          for (int d = 0; d < DIM; ++d)
+            if ((q[d] < 0 || q[d] >= a.L.n[d]) && !a.B.periodic[d]) wall = true;
+          if (wall) continue;  // a ghost has no residual
         }
-  }
+        gather(wrap(a.L, x));
+      }
   const long m = p.c;
   a.Hb[m] += acc[0];
   if (R) a.Zb[m] += acc[1];
@@ -623,37 +586,295 @@ __global__ void __launch_bounds__(kBlock) k_adj_resid(AdjResidArgs a) {
     a.vb[d][m] += acc[1 + R + d];
     // the high face of the last cell: a state flux on an outflow side, a
     // constant on a wall or inflow side
-    if (!W || a.B.periodic[d] || pm[d] + 1 < a.L.n[d] || a.B.kind[d][1] == LM_SIDE_OUTFLOW)
+    if (a.B.periodic[d] || pm[d] + 1 < a.L.n[d] || a.B.kind[d][1] == LM_SIDE_OUTFLOW)
       a.Fb[d][m] += acc[1 + R + DIM + d];
   }
 }
 
-static void launch_resid_sel(hipStream_t st, const AdjResidArgs &a, int W) {
-  const dim3 g = grid_for(a.L), bl(kBX, kBY);
-  const int sel = (a.L.ndim == 3 ? 4 : 0) + (a.P.reacting ? 2 : 0) + W;
-  switch (sel) {
-    case 0: hipLaunchKernelGGL((k_adj_resid<2, 0, 0>), g, bl, 0, st, a); break;
-    case 1: hipLaunchKernelGGL((k_adj_resid<2, 0, 1>), g, bl, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_adj_resid<2, 1, 0>), g, bl, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((k_adj_resid<2, 1, 1>), g, bl, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_adj_resid<3, 0, 0>), g, bl, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((k_adj_resid<3, 0, 1>), g, bl, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((k_adj_resid<3, 1, 0>), g, bl, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_adj_resid<3, 1, 1>), g, bl, 0, st, a); break;
+static void launch_resid_sides(hipStream_t st, const AdjResidArgs &a) {
+  LM_ADJ_LAUNCH(k_adj_resid, a.L, a.P.reacting, a);
+}
+
+// Away from sides (every cell of a periodic grid) the transpose in closed
+// form. The residuals are sums over faces, so with the cotangents carried to
+// the cells as a = RbH/rho, z = RbZ/rho, b_c = Rb_vc, a face between cells x
+// and y = x + d (flux F, G = (H_y - H_x)/h, K the mean kappa) contributes
+//   -F G (a_x + a_y)/2 + K G (a_x - a_y)/(h Pe)                 of R_H,
+//   -F (v_x + v_y)/2 . (b_x - b_y)/h + t . tau                  of R_v,
+// with t_c = Pr/Pe (b_cx - b_cy)/h, and like terms of R_Z with the weights z
+// and z/(le Pe) + a nn/Pe; the derivatives of these with respect to H, Z, v,
+// F at cell m are collected from the faces whose values reach m. The plane
+// (d, k) of 9 cells around m holds all that the mixed derivatives of tau on
+// d-faces read, so the values of one plane are in registers at a time. Some
+// 800 operations per cell in 3D, against 27 residuals with 7 derivatives
+// each when they are evaluated with dual numbers as in the band along the
+// sides: 128^3 254 us (dual numbers 1723 us, bound by their arithmetic at one
+// wavefront per unit), 512^2 15.1 us (35.9 us). Bound by the latency of some
+// 130 cached loads per cell at two to three wavefronts per unit.
+// Quotients of constants, formed once on the host: uniform operands of the
+// kernel then come from scalar registers.
+struct ResidConst {
+  double ih[3], nu, iPe, iPeDa, ip0;
+};
+template <int DIM, int R>
+__global__ void __launch_bounds__(kBlock, R ? 2 : 3) k_adj_resid_in(AdjResidArgs a, ResidConst C) {
+  CellPos p;
+  if (!cell_of_thread(a.L, p)) return;
+  if (a.box_mode) {
+    const bool in = p.i >= a.box_lo[0] && p.i <= a.box_hi[0] && p.j >= a.box_lo[1] && p.j <= a.box_hi[1] &&
+                    p.k >= a.box_lo[2] && p.k <= a.box_hi[2];
+    if (!in) return;
   }
+  const AdjPhys &P = a.P;
+  // A wavefront lies in one row of cells, so a neighbour is a row, whose
+  // address is uniform, and one of three byte offsets in it: indices 0 (low),
+  // 1 (self), 2 (high) per direction.
+  const unsigned ob[3] = {8u * (p.i > 0 ? p.i - 1 : a.L.n[0] - 1), 8u * p.i,
+                          8u * (p.i + 1 < a.L.n[0] ? p.i + 1 : 0)};
+  long orow[2][3];
+  const int pm[2] = {__builtin_amdgcn_readfirstlane(p.j), __builtin_amdgcn_readfirstlane(p.k)};
+#pragma unroll
+  for (int d = 1; d < DIM; ++d) {
+    const int q = pm[d - 1], n = a.L.n[d];
+    orow[d - 1][0] = (q > 0 ? q - 1 : n - 1) * a.L.s[d];
+    orow[d - 1][1] = q * a.L.s[d];
+    orow[d - 1][2] = (q + 1 < n ? q + 1 : 0) * a.L.s[d];
+  }
+  if (DIM == 2) orow[1][0] = orow[1][1] = orow[1][2] = 0;
+  struct At {
+    long row;
+    unsigned b;
+  };
+  auto at2 = [&](int d, int e, int k, int f) __attribute__((always_inline)) {  // offset e along d and f along k
+    const int x = d == 0 ? e : (k == 0 ? f : 1), y = d == 1 ? e : (k == 1 ? f : 1), z = d == 2 ? e : (k == 2 ? f : 1);
+    return At{a.L.base + orow[0][y] + orow[1][z], ob[x]};
+  };
+  auto get = [](const double *v, At x) __attribute__((always_inline)) {
+    return *(const double *)((const char *)(v + x.row) + x.b);
+  };
+  auto add = [](double *v, At x, double y) __attribute__((always_inline)) {
+    *(double *)((char *)(v + x.row) + x.b) += y;
+  };
+  const At m = at2(0, 1, 1, 1);
+  auto nb = [&](int d, int e) __attribute__((always_inline)) { return at2(d, e, (d + 1) % 3, 1); };
+  double hb = 0.0, zb = 0.0, kb = 0.0;  // cotangents of H, Z, kappa
+  double vb[DIM], fb[DIM];              // of v and of the flux on the high face
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) vb[d] = fb[d] = 0.0;
+
+  // scalars: weights of cell x
+  struct W {
+    double H, Z, a, z, w;  // w: weight of the diffusion of Z
+  };
+  auto weights = [&](At x) __attribute__((always_inline)) {
+    W r;
+    r.H = get(a.H, x);
+    if (R) {
+      r.Z = get(a.Z, x);
+      const double ir = P.qs * (ftilde_of(P, r.Z) + r.H) * C.ip0;
+      r.a = get(a.RbH, x) * ir;
+      r.z = get(a.RbZ, x) * ir;
+      const double th = 0.5 * (1.0 + tanh(P.k * (r.Z - 1.0)));
+      r.w = (r.z / ((P.Le_F - P.Le_O) * th + P.Le_O) + r.a * ((P.N_F - P.N_O) * th + P.N_O)) * C.iPe;
+    } else {
+      r.Z = r.z = r.w = 0.0;
+      r.a = get(a.RbH, x) * (P.qs * (r.H - 1.0) * C.ip0);
+    }
+    return r;
+  };
+  const W wm = weights(m);
+  const double km = get(a.kap, m);
+  double F[DIM][2], kf[DIM][2];  // flux and kappa on the low and high face
+  double advH = 0.0, difH = 0.0, advZ = 0.0, difZ = 0.0;
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    const double ih = C.ih[d];
+    F[d][0] = get(a.F[d], nb(d, 0));
+    F[d][1] = get(a.F[d], m);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const W wn = weights(nb(d, 2 * s));
+      kf[d][s] = 0.5 * (km + get(a.kap, nb(d, 2 * s)));
+      const double sg = s ? 1.0 : -1.0;
+      // a difference across the face is taken towards high, sg (n - m)
+      const double G = sg * (wn.H - wm.H) * ih, sa = 0.5 * (wm.a + wn.a);
+      const double da = sg * (wm.a - wn.a) * ih * C.iPe;
+      hb -= sg * ih * (kf[d][s] * da - F[d][s] * sa);
+      kb += 0.5 * G * da;
+      if (s) fb[d] -= G * sa;
+      advH += 0.5 * F[d][s] * G;
+      difH += sg * kf[d][s] * G * ih;
+      if (R) {
+        const double Gz = sg * (wn.Z - wm.Z) * ih, sz = 0.5 * (wm.z + wn.z);
+        const double dw = sg * (wm.w - wn.w) * ih;
+        zb -= sg * ih * (kf[d][s] * dw - F[d][s] * sz);
+        kb += 0.5 * Gz * dw;
+        if (s) fb[d] -= Gz * sz;
+        advZ += 0.5 * F[d][s] * Gz;
+        difZ += sg * kf[d][s] * Gz * ih;
+      }
+    }
+  }
+  // the cell's own terms
+  double dft = 0.0, T;
+  if (R) {
+    T = P.qs * (ftilde_of(P, wm.Z) + wm.H);
+    dft = dftilde_of(P, wm.Z);
+  } else {
+    T = P.qs * (wm.H - 1.0);
+  }
+  double rH = -advH + difH * C.iPe, tb = 0.0;
+  const double chi = a.chi ? (double)a.chi[p.c] : 0.0;
+  const double dh = chi != 0.0 ? chi * (wm.H - (a.H_ib ? get(a.H_ib, m) : 0.0)) * C.iPeDa : 0.0;
+  rH -= km * dh;
+  kb -= wm.a * dh;
+  hb -= wm.a * km * chi * C.iPeDa;
+  if (R) {
+    const double t = tanh(P.k * (wm.Z - 1.0)), th = 0.5 * (1.0 + t), dth = 0.5 * P.k * (1.0 - t * t);
+    const double ile = 1.0 / ((P.Le_F - P.Le_O) * th + P.Le_O), nn = (P.N_F - P.N_O) * th + P.N_O;
+    const double dz = chi != 0.0 ? chi * (wm.Z - (a.Z_ib ? get(a.Z_ib, m) : 0.0)) * C.iPeDa : 0.0;
+    const double u = difZ * C.iPe - km * dz;
+    rH += nn * difZ * C.iPe;
+    const double rZ = -advZ + u * ile;
+    kb -= wm.z * ile * dz;
+    zb -= wm.z * ile * km * chi * C.iPeDa;
+    zb += dth * (wm.a * (P.N_F - P.N_O) * difZ * C.iPe - wm.z * u * ile * ile * (P.Le_F - P.Le_O));
+    tb = get(a.RbZ, m) * rZ * C.ip0;
+  }
+  tb += get(a.RbH, m) * rH * C.ip0;
+  const double b1 = get(a.Rbv[1], m);
+  if (P.inv_Fr2 != 0.0) tb += b1 * P.inv_Fr2 * P.p0 / (T * T);
+  if (chi != 0.0) {
+    const double g = chi * P.Pr * C.iPeDa;
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+      const double bc = get(a.Rbv[c], m);
+      vb[c] -= g * km * bc;
+      kb -= g * bc * (get(a.v[c], m) - (a.v_ib[c] ? get(a.v_ib[c], m) : 0.0));
+    }
+  }
+  // each part's sums are finished before the next is read (the compiler
+  // would otherwise hold several planes and spill)
+  auto fence = [&]() __attribute__((always_inline)) {
+    asm volatile("" : "+v"(kb), "+v"(hb), "+v"(tb) : : "memory");
+    if (R) asm volatile("" : "+v"(zb), "+v"(dft) : : "memory");
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) asm volatile("" : "+v"(vb[d]), "+v"(fb[d]) : : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // momentum: convection and stress
+  const double nu = C.nu;
+  // face values of a pair of cells along d: component c on the low (s = 0)
+  // and high face, for the terms of derivative D[d][c]
+  auto normal = [&](int d, int c, int s, double bl, double bh, double vl, double vh, double ih) __attribute__((
+                      always_inline)) {
+    const double db = (bl - bh) * ih;
+    const double f = F[d][s] * db;
+    const double t = nu * db;
+    vb[c] -= 0.5 * f;
+    if (s) fb[d] -= 0.5 * (vl + vh) * db;
+    const double S = (d == c ? 4.0 / 3.0 : 1.0) * kf[d][s] * t * ih;
+    vb[c] += s ? -S : S;
+    return t;
+  };
+  auto plane = [&](auto DD_, auto KK_) __attribute__((always_inline)) {
+    constexpr int d0 = decltype(DD_)::value, k0 = decltype(KK_)::value;
+    double kp[3][3], b0[3][3], b1[3][3], v0[3][3], v1[3][3];  // [offset along d0][along k0]
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+      for (int f = 0; f < 3; ++f) {
+        const At x = at2(d0, e, k0, f);
+        kp[e][f] = get(a.kap, x);
+        b0[e][f] = get(a.Rbv[d0], x);
+        b1[e][f] = get(a.Rbv[k0], x);
+        v0[e][f] = get(a.v[d0], x);
+        v1[e][f] = get(a.v[k0], x);
+      }
+    // faces of direction d, with the other direction of the plane k: bd, vd
+    // the components along d, bk, vk along k, indexed [along d][along k]
+    auto pair = [&](int d, int k, auto K, auto bd, auto vd, auto bk, auto vk) __attribute__((always_inline)) {
+      const double ihd = C.ih[d], q = 0.25 * C.ih[k];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const double tk = normal(d, k, s, bk(s, 1), bk(s + 1, 1), vk(s, 1), vk(s + 1, 1), ihd);
+        const double td = nu * ihd * (bd(s, 1) - bd(s + 1, 1));
+        const double Ddk = (vk(s + 1, 1) - vk(s, 1)) * ihd;
+        const double Dkd = q * ((vd(s, 2) - vd(s, 0)) + (vd(s + 1, 2) - vd(s + 1, 0)));
+        const double Dkk = q * ((vk(s, 2) - vk(s, 0)) + (vk(s + 1, 2) - vk(s + 1, 0)));
+        kb += 0.5 * (tk * (Ddk + Dkd) - (2.0 / 3.0) * td * Dkk);
+        // the face one cell below (f = 0) or above (f = 2) m along k
+#pragma unroll
+        for (int f = 0; f < 3; f += 2) {
+          const double g = (f ? -q : q) * 0.5 * (K(s, f) + K(s + 1, f)) * nu * ihd;
+          vb[d] += g * (bk(s, f) - bk(s + 1, f));
+          vb[k] -= (2.0 / 3.0) * g * (bd(s, f) - bd(s + 1, f));
+        }
+      }
+    };
+    pair(
+        d0, k0, [&](int e, int f) { return kp[e][f]; }, [&](int e, int f) { return b0[e][f]; },
+        [&](int e, int f) { return v0[e][f]; }, [&](int e, int f) { return b1[e][f]; },
+        [&](int e, int f) { return v1[e][f]; });
+    pair(
+        k0, d0, [&](int e, int f) { return kp[f][e]; }, [&](int e, int f) { return b1[f][e]; },
+        [&](int e, int f) { return v1[f][e]; }, [&](int e, int f) { return b0[f][e]; },
+        [&](int e, int f) { return v0[f][e]; });
+    // the components along their own faces, each direction once
+    auto own = [&](int d, auto b, auto v) __attribute__((always_inline)) {
+      const double ihd = C.ih[d];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const double t = normal(d, d, s, b(s), b(s + 1), v(s), v(s + 1), ihd);
+        kb += (2.0 / 3.0) * t * (v(s + 1) - v(s)) * ihd;
+      }
+    };
+    if (k0 == d0 + 1) own(d0, [&](int e) { return b0[e][1]; }, [&](int e) { return v0[e][1]; });
+    if (k0 == DIM - 1 && d0 == DIM - 2) own(k0, [&](int e) { return b1[1][e]; }, [&](int e) { return v1[1][e]; });
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, DIM - 1>;
+  fence();
+  plane(I0(), I1());
+  fence();
+  if constexpr (DIM == 3) {
+    plane(I1(), I2());
+    fence();
+    plane(I0(), I2());
+    fence();
+  }
+
+  tb += kb * get(a.dkap, m);
+  add(a.Hb, m, hb + P.qs * tb);
+  if (R) add(a.Zb, m, zb + P.qs * dft * tb);
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    add(a.vb[d], m, vb[d]);
+    add(a.Fb[d], m, fb[d]);
+  }
+}
+
+static void launch_resid_in(hipStream_t st, const AdjResidArgs &a) {
+  ResidConst c{};
+  for (int d = 0; d < a.L.ndim; ++d) c.ih[d] = 1.0 / a.P.h[d];
+  c.nu = a.P.Pr / a.P.Pe;
+  c.iPe = 1.0 / a.P.Pe;
+  c.iPeDa = a.chi ? 1.0 / (a.P.Pe * a.P.Da) : 0.0;
+  c.ip0 = 1.0 / a.P.p0;
+  LM_ADJ_LAUNCH(k_adj_resid_in, a.L, a.P.reacting, a, c);
 }
 
 // With wall, inflow or outflow sides: the cells whose readers' stencils
 // stay inside the grid (at least 2 cells from every non-periodic side, 3
-// from a high outflow side, whose gather reaches further) take the
-// periodic kernel, exact there (no ghost is read and no position wraps
-// across such a side); the band along those sides the kernel with the
-// ghost rules.
+// from a high outflow side, whose gather reaches further) take the closed
+// form, exact there (no ghost is read and no position wraps across such a
+// side); the band along those sides the kernel with the ghost rules.
 hipError_t launch_adj_resid(hipStream_t st, const AdjResidArgs &a0) {
   AdjResidArgs a = a0;
   a.box_mode = 0;
   if (a.B.all_periodic) {
-    launch_resid_sel(st, a, 0);
+    launch_resid_in(st, a);
     return hipGetLastError();
   }
   bool empty = false;
@@ -668,10 +889,10 @@ hipError_t launch_adj_resid(hipStream_t st, const AdjResidArgs &a0) {
   }
   if (!empty) {
     a.box_mode = 1;
-    launch_resid_sel(st, a, 0);
+    launch_resid_in(st, a);
     a.box_mode = 2;
   }
-  launch_resid_sel(st, a, 1);
+  launch_resid_sides(st, a);
   return hipGetLastError();
 }
 

@@ -762,3 +762,19 @@ def test_taped_levels_reverse_sweep_is_bit_exact(kind):
         s.save_step_levels()
     assert e.value.status == lib.LM_ESTATE
 
+
+
+@pytest.mark.parametrize("n", [(8, 4), (68, 6), (4, 8, 4), (66, 6, 4)], ids=str)
+@pytest.mark.parametrize("react", [False, True], ids=["inert", "reacting"])
+def test_adjoint_step_dot_product_edges(n, react):
+    """Rows shorter than a wavefront, a second wavefront of two or four
+    cells, sides of four cells whose neighbours wrap from both ends."""
+    from workloads.ics import reacting_periodic_case
+    case = reacting_periodic_case(n, seed=17)
+    if not react:
+        for k in ("reacting", "S", "qs", "eps", "tol", "Le_F", "Le_O"):
+            case.params.pop(k, None)
+        rng = np.random.default_rng(18)
+        case.Z, case.H, case.T = None, None, 1.0 + rng.random(case.v[0].shape)
+    print("adjoint dot edges", n, react, flush=True)
+    _dot_product_check(case, True, inv_Fr2=0.5, seed=500 + sum(n))
