@@ -1271,6 +1271,55 @@ AdjPhys adj_phys(const lm_ctx *c) {
   return P;
 }
 
+// Whether the `bytes` at buf are memory of the context's device, inside one
+// allocation and aligned to 8 bytes: what a kernel may read and write. Any
+// other buffer is left to the copy call, which takes or refuses it.
+bool device_span(const void *buf, size_t bytes) {
+  hipPointerAttribute_t at{};
+  int dev = -1;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if ((uintptr_t)buf % 8 != 0) return false;
+  if (hipPointerGetAttributes(&at, buf) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+      at.type != hipMemoryTypeDevice || at.device != dev ||
+      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)buf) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t off = (const char *)buf - (const char *)base;
+  return off <= size && bytes <= size - off;
+}
+
+// k arrays of the context copied from (in) or to a caller's buffer that
+// holds them one after another.
+hipError_t copy_arrays(lm_ctx *c, double *const *arr, int k, void *buf, bool in) {
+  const size_t n = (size_t)c->lay.total;
+  if (!device_span(buf, k * n * 8)) {
+    for (int q = 0; q < k; ++q) {
+      char *b = (char *)buf + q * n * 8;
+      const hipError_t e = in ? hipMemcpyAsync(arr[q], b, n * 8, hipMemcpyDeviceToDevice, c->st)
+                              : hipMemcpyAsync(b, arr[q], n * 8, hipMemcpyDeviceToDevice, c->st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  CopyMany a{};
+  a.n = (long)n;
+  for (int q = 0; q < k; ++q) {
+    double *b = (double *)buf + q * n;
+    a.src[q] = in ? b : arr[q];
+    a.dst[q] = in ? arr[q] : b;
+  }
+  return launch_copy_many(c->st, a, k);
+}
+
+hipError_t clear_arrays(lm_ctx *c, double *const *arr, int k) {
+  CopyMany a{};
+  a.n = c->lay.total;
+  for (int q = 0; q < k; ++q) a.dst[q] = arr[q];
+  return launch_copy_many(c->st, a, k);
+}
+
 }  // namespace
 
 extern "C" lm_status lm_state_size(const lm_ctx *c, size_t *bytes) {
@@ -1291,9 +1340,7 @@ extern "C" lm_status lm_save_state(lm_ctx *c, void *buf) {
                 c->nsame,    c->pc_used};
   HIPCHK(c, hipMemcpyAsync(buf, &h, sizeof(h), hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemcpyAsync((char *)buf + 128, c->p0d, sizeof(P0Dev), hipMemcpyDeviceToDevice, c->st));
-  char *p = (char *)buf + 256;
-  const size_t ab = (size_t)c->lay.total * 8;
-  for (int q = 0; q < k; ++q) HIPCHK(c, hipMemcpyAsync(p + q * ab, arr[q], ab, hipMemcpyDeviceToDevice, c->st));
+  HIPCHK(c, copy_arrays(c, arr, k, (char *)buf + 256, false));
   HIPCHK(c, hipStreamSynchronize(c->st));
   return LM_OK;
 }
@@ -1305,9 +1352,7 @@ extern "C" lm_status lm_load_state(lm_ctx *c, const void *buf) {
   StateHeader h;
   HIPCHK(c, hipMemcpyAsync(&h, buf, sizeof(h), hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipMemcpyAsync(c->p0d, (const char *)buf + 128, sizeof(P0Dev), hipMemcpyDeviceToDevice, c->st));
-  const char *p = (const char *)buf + 256;
-  const size_t ab = (size_t)c->lay.total * 8;
-  for (int q = 0; q < k; ++q) HIPCHK(c, hipMemcpyAsync(arr[q], p + q * ab, ab, hipMemcpyDeviceToDevice, c->st));
+  HIPCHK(c, copy_arrays(c, arr, k, (char *)buf + 256, true));
   HIPCHK(c, hipStreamSynchronize(c->st));
   c->have_prev = h.have_prev;
   c->have_state = h.have_state;
@@ -1353,8 +1398,7 @@ extern "C" lm_status lm_adjoint_seed_ke(lm_ctx *c) {
   double *arr[14];
   int fd[14];
   const int k = adj_arrays(a, nd, c->prm.reacting, arr, fd);
-  const size_t ab = (size_t)c->lay.total * 8;
-  for (int q = 0; q < k; ++q) HIPCHK(c, hipMemsetAsync(arr[q], 0, ab, c->st));
+  HIPCHK(c, clear_arrays(c, arr, k));
   c->aw.xa_valid[0] = c->aw.xa_valid[1] = 0;  // a new reverse sweep: no warm start
   Level &lv = c->lev[c->icur];
   AdjCellArgs g{};
@@ -1466,9 +1510,7 @@ extern "C" lm_status lm_save_step_levels(lm_ctx *c, void *buf) {
   double *arr[16];
   // after a committed step the new level is the current one
   const int k = step_level_arrays(c, c->lev[c->istar], c->lev[c->icur], arr);
-  const size_t ab = (size_t)c->lay.total * 8;
-  for (int q = 0; q < k; ++q)
-    HIPCHK(c, hipMemcpyAsync((char *)buf + q * ab, arr[q], ab, hipMemcpyDeviceToDevice, c->st));
+  HIPCHK(c, copy_arrays(c, arr, k, buf, false));
   HIPCHK(c, hipStreamSynchronize(c->st));
   return LM_OK;
 }
@@ -1489,15 +1531,13 @@ static lm_status step_adjoint(lm_ctx *c, const void *levels) {
   const Lay &L = c->lay;
   const int nd = c->grid.ndim;
   const bool react = c->prm.reacting;
-  const size_t ab = (size_t)L.total * 8;
   lm_status s = LM_OK;
   if (levels) {
     // the step's predicted and new levels as saved right after it was
     // taken from this state
     double *arr[16];
     const int k = step_level_arrays(c, c->lev[c->istar], c->lev[c->inxt], arr);
-    for (int q = 0; q < k; ++q)
-      HIPCHK(c, hipMemcpyAsync(arr[q], (const char *)levels + q * ab, ab, hipMemcpyDeviceToDevice, c->st));
+    HIPCHK(c, copy_arrays(c, arr, k, (void *)levels, true));
   } else {
     // forward recompute of the step (state at n untouched: outputs go to the
     // predicted and next levels)
@@ -1515,10 +1555,13 @@ static lm_status step_adjoint(lm_ctx *c, const void *levels) {
   AdjState &aout = c->ad[c->ad_cur ^ 1];   // cotangent of the step's inputs
   AdjWork &w = c->aw;
   // zero what is accumulated into
-  HIPCHK(c, hipMemsetAsync(w.Hb_star, 0, ab, c->st));
-  if (react) HIPCHK(c, hipMemsetAsync(w.Zb_star, 0, ab, c->st));
+  double *zero[11];
+  int nz = 0;
+  zero[nz++] = w.Hb_star;
+  if (react) zero[nz++] = w.Zb_star;
   for (int d = 0; d < nd; ++d)
-    for (double *z : {w.vb_star[d], w.Fb_star[d], aout.F[d]}) HIPCHK(c, hipMemsetAsync(z, 0, ab, c->st));
+    for (double *z : {w.vb_star[d], w.Fb_star[d], aout.F[d]}) zero[nz++] = z;
+  HIPCHK(c, clear_arrays(c, zero, nz));
   // the stage's adjoint solve starts from its solution one step later in
   // time (the previous call's), which the pressure cotangents of
   // consecutive steps leave close; the tolerance is the same
@@ -1534,9 +1577,8 @@ static lm_status step_adjoint(lm_ctx *c, const void *levels) {
     HIPCHK(c, poisson_solve(c->st, c->pws, rhs, x0, c->prm.poisson_rtol, c->prm.poisson_maxit, w.xa_iters[stage],
                             &iters, &relres, &conv));
     if (!conv) return fail(c, LM_ENOCONV, "adjoint Poisson solve did not converge");
-    HIPCHK(c, launch_shift(c->st, L, c->pws.x, c->pws.sc, out));
     std::swap(w.xa[stage], w.xa_old[stage]);
-    HIPCHK(c, hipMemcpyAsync(w.xa[stage], out, ab, hipMemcpyDeviceToDevice, c->st));
+    HIPCHK(c, launch_shift(c->st, L, c->pws.x, c->pws.sc, out, 0, w.xa[stage]));
     w.xa_valid[stage] = w.xa_valid[stage] + 1 > 2 ? 2 : w.xa_valid[stage] + 1;
     w.xa_iters[stage] = iters;
     return LM_OK;

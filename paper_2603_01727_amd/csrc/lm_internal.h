@@ -283,7 +283,14 @@ hipError_t launch_adj_extrap(hipStream_t st, const Lay &L, const double *x1, con
 hipError_t launch_adj_outflow(hipStream_t st, const Lay &L, const AdjPhys &P, int d, double *y, const double *Fb,
                               double *scratch);
 hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const SolverScalars *sc, double *out,
-                        int gated = 0);
+                        int gated = 0, double *out2 = nullptr);  // out2: a second copy of out
+// The same n doubles of up to 32 arrays copied, or cleared where src is null.
+struct CopyMany {
+  const double *src[32];
+  double *dst[32];
+  long n;
+};
+hipError_t launch_copy_many(hipStream_t st, const CopyMany &a, int k);
 
 // ---- Poisson (lm_solver.hip) -----------------------------------------------
 // Bump allocator over the caller workspace; with base == nullptr it only
