@@ -608,9 +608,9 @@ static void launch_resid_sides(hipStream_t st, const AdjResidArgs &a) {
 // d-faces read, so the values of one plane are in registers at a time. Some
 // 800 operations per cell in 3D, against 27 residuals with 7 derivatives
 // each when they are evaluated with dual numbers as in the band along the
-// sides: 128^3 254 us (dual numbers 1723 us, bound by their arithmetic at one
-// wavefront per unit), 512^2 15.1 us (35.9 us). Bound by the latency of some
-// 130 cached loads per cell at two to three wavefronts per unit.
+// sides: 128^3 254 us (dual numbers 1723 us), 512^2 15.1 us (35.9 us). Some
+// 130 cached loads per cell at two to three wavefronts per unit
+// are what remains.
 // Quotients of constants, formed once on the host: uniform operands of the
 // kernel then come from scalar registers.
 struct ResidConst {
