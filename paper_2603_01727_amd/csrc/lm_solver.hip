@@ -1000,12 +1000,19 @@ static void fit_tile(const Lay &L, int nu, const int (*cand)[2], int nc, int &tx
   }
 }
 
+// The finest level takes the large tile, whose frame is 1.9 times its cells
+// (the small one's 2.9), once the chip has one and a half per unit; below
+// that the small one puts more wavefronts on a unit. FP64 solve, large and
+// small: 256^2 478 and 404 us, 512^2 599 and 529, 768 x 512 1268 and 1186,
+// 1024 x 512 2313 and 2308, 1024 x 768 1109 and 1216, 1024^2 840 and 1018.
+constexpr int kLargeTiles = 384;
+
 static void choose_tile(PoissonWS &ws, int l) {
   const Lay &L = ws.lev[l].lay;
   ws.tx[l] = ws.ty[l] = 0;
   if (ws.met || L.ndim != 2 || ws.nu < 1 || ws.nu > 3 || l >= ws.lc) return;
   const int cand[3][2] = {{TX, TY}, {TXS, TYS}, {16, 16}};
-  const int q = l == 0 ? 0 : 1;
+  const int q = l == 0 && tiles2d(L, TX, TY) > kLargeTiles ? 0 : 1;
   fit_tile(L, ws.nu, cand + q, 3 - q, ws.tx[l], ws.ty[l]);
 }
 
@@ -1329,8 +1336,8 @@ static void launch_nu_vc(int nu, Up2DArgs<T> &a, dim3 g, hipStream_t st, bool ex
   else if (nu == 2) hipLaunchKernelGGL((k_mg_up2d<T, 2, 0, TXT, TYT, true>), g, dim3(kBlock), 0, st, a);
   else hipLaunchKernelGGL((k_mg_up2d<T, 3, 0, TXT, TYT, true>), g, dim3(kBlock), 0, st, a);
 }
-// Level 0 runs the large tile, coarser levels the small one; the
-// variable-coefficient kernels run the small tiles only.
+// Level 0 runs the large tile where it has enough of them, other levels the
+// small one; the variable-coefficient kernels run the small tiles only.
 template <typename T>
 static void launch_nu(const PoissonWS &ws, int l, int nu, Down2DArgs<T> &a, hipStream_t st, hipEvent_t e0 = nullptr,
                       hipEvent_t e1 = nullptr) {
