@@ -29,7 +29,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2603_01727_amd", "csrc", f)
-                  for f in ("lm_mg_kernels.h", "lm_mg3d.h", "lm_solver.hip")]
+                  for f in ("lm_mg_kernels.h", "lm_mg3d.h", "lm_coarse.h", "lm_solver.hip")]
 
 # Kernel classes timed inside the step (lm_kernel_timing) and their
 # algorithmic HBM bytes per finest-level cell (FP64 build, mixed build):
@@ -496,18 +496,18 @@ def summarize_trace(db_path):
               f"mean {sum(fw) / len(fw):9.2f}  total {sum(d) / 1e3:8.3f}  vgpr {r['vgpr']:3d} lds {r['lds']:6d} "
               f"scratch {r['scratch']}")
     # the single-reduction CG update by iteration: the first launch after a
-    # solve's initialisation kernel is iteration 1 (no old p, s: fewer bytes)
+    # solve's initialisation kernel is iteration 1 (no old p: fewer bytes)
     seq = db.execute("select name, end - start from kernels order by start").fetchall()
     it, by_k = 0, {}
     for name, dur in seq:
         if "k_cg_init" in name:
             it = 0
-        elif "k_cgcg_update" in name:
+        elif "k_cgcg_march" in name:
             it += 1
             by_k.setdefault(min(it, 2), []).append(dur * 1e-3)
     for k, d in sorted(by_k.items()):
         fw = _full_work(d)
-        print(f"k_cgcg_update iteration {'1' if k == 1 else '>= 2'}: n {len(d)}, full-work n {len(fw)} "
+        print(f"k_cgcg_march iteration {'1' if k == 1 else '>= 2'}: n {len(d)}, full-work n {len(fw)} "
               f"mean {sum(fw) / len(fw):.2f} us")
     # time between consecutive dispatches (end of one to start of the next)
     # inside the runs of work, i.e. leaving out pauses of 1 ms and more
@@ -564,7 +564,7 @@ def summarize_pmc(fetch_db, write_db, traffic_out=None):
         pick = {}
         for (name, grid), tot in out.items():
             for which, tag in ((0, "k_mg_down3d<double"), (1, "k_mg_up3d<double, 2, 1"),
-                               (2, "k_cgcg_update<3, double")):
+                               (2, "k_cgcg_march<double")):
                 if tag in name and (which not in pick or grid > pick[which][1]):
                     pick[which] = (name, grid, tot)
         rec = {"workload": "3D periodic 256^3 FP64 step", "fetch_scale": round(fs, 4), "write_scale": round(ws, 4),

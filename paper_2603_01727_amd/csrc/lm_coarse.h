@@ -14,7 +14,7 @@
 // Levels of at most 64 blocks run in the first wavefront alone, which needs
 // no barriers. The pseudo-inverse of the coarsest level sits in LDS (at
 // most 64 cells) or is read by columns of 64-lane rows (it is symmetric),
-// eight loads in flight.
+// eight loads in flight, 32 in 3D.
 //
 // What bounds it: latency (one workgroup; about 30 dependent phases of one
 // LDS round trip and a few FP64 operations each), on the largest level the

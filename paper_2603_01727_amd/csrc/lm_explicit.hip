@@ -1303,10 +1303,10 @@ hipError_t launch_shift(hipStream_t st, const Lay &L, const double *x, const Sol
   return hipGetLastError();
 }
 
-// One launch copies (src null: clears) all the arrays of a state: 128^3, 14
-// arrays of 18 MB, 88 us (5.6 TB/s) where a copy call for each took 10 to
-// 15 us per array; 512^2 10 us against 3 us per array and the gaps between
-// the calls. Arrays begin at odd multiples of 8 bytes in a caller's
+// One launch copies (src null: clears) all the arrays of a state. Mean over
+// the launches of a gradient (states of 16 arrays, levels of 13, clears of
+// 10): 128^3 88 us, 512^2 10 us, where a copy or fill call for each array
+// took 10 to 15 us and 3 us, and a gap. Arrays begin at odd multiples of 8 bytes in a caller's
 // buffer, so a lane moves 8 bytes; four loads are in flight per lane.
 __global__ void __launch_bounds__(256) k_copy_many(CopyMany a) {
   const double *src = a.src[blockIdx.y];

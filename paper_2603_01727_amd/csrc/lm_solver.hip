@@ -501,8 +501,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_rz(CGArgs a) {
 // arrays to move; and x takes its update every second step, both directions
 // at once, when the old p is read anyway (x += alpha_{k-1} p_{k-1} +
 // alpha_k p_k on even steps, the pending one when the solve ends on an odd
-// one). 48 B per cell and step instead of 80: 256^3 FP64 145 us (5.5 TB/s)
-// instead of 217 us.
+// one). 48 B per cell and step instead of 80: 256^3 FP64 168 us in step (4.8
+// TB/s, the rate of a large copy) instead of 257 us.
 struct CgScalars {
   double alpha, beta, alpha_old;
   bool end, pending;  // the solve ends with this test; x lacks alpha_{k-1} p_{k-1}
