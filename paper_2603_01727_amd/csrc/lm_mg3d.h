@@ -369,14 +369,6 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_up3d(Fused3DArgs<T> a) {
   };
   static_for<0, D>([&](auto J) __attribute__((always_inline)) { fetch(t0 + decltype(J)::value, J); });
   double ru = 0.0, wu = 0.0, rr = 0.0;
-  // EXTRA: r of the w stage's next plane, in flight one step ahead
-  double rn0 = 0.0, rn1 = 0.0;
-  auto fetch_r = [&](int q) __attribute__((always_inline)) {
-    const double2 v = *(const double2 *)((const double *)a.b + a.Lf.base + (long)wrap_any(q, p.nz) * s2 + p.xy);
-    rn0 = v.x;
-    rn1 = v.y;
-  };
-  if (EXTRA) fetch_r(t0 - S - 1);
   auto step = [&](auto U, int ts) __attribute__((always_inline)) {
     constexpr int u = decltype(U)::value;
     const int t = t0 + ts;
@@ -431,8 +423,6 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_up3d(Fused3DArgs<T> a) {
     if (EXTRA) {
       // w = A u on plane q = t - S - 1, both cells, in FP64
       const int q = t - S - 1;
-      const double r0 = rn0, r1 = rn1;
-      fetch_r(q + 1);
       constexpr int k = Slot<kRing, u, S + 1>::v;
       constexpr int km = Slot<kRing, u, S + 2>::v, kp = Slot<kRing, u, S>::v;
       if (q >= p.z0 && q < p.z0 + p.zc) {
@@ -455,7 +445,9 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_up3d(Fused3DArgs<T> a) {
           T *o = a.xout + g;
           o[0] = pick<T>(cr, XB[k], XR[k]);
           o[1] = pick<T>(cr, XR[k], XB[k]);
-          const double rR = pick<double>(cr, r1, r0), rB = pick<double>(cr, r0, r1);
+          // the ring still holds plane q of r (a second read of it: 256^3
+          // 174 us instead of 147, 128^3 29.8 instead of 27.5)
+          const double rR = (double)BR[k], rB = (double)BB[k];
           ru += rR * uR + rB * uB;
           wu += wR * uR + wB * uB;
           rr += rR * rR + rB * rB;
