@@ -113,7 +113,9 @@ struct SolverScalars {
   double alh[2];     // alpha of the last two iterations (single-reduction CG)
   double rr, cc;     // last ||r||^2 and ||c||^2 (c: mean-free right-hand side)
   double mean_b, sum_b, outflow_c, mean_x;
-  int done, iters, zero, nonconv;  // kept contiguous (cleared together)
+  // kept contiguous (cleared together); done: nonzero when the solve has
+  // ended (k + 1 when the test of CG step k ended it)
+  int done, iters, zero, nonconv;
   int rho_bad;                     // a density given for beta = 1/rho_f is not positive and finite
 };
 

@@ -289,7 +289,8 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
   __shared__ T bs[W * HH];
   __shared__ T fx[WV], fy[WV], ig[WV];
   __shared__ double sh[kBlock / 64];
-  if (a.sc->done) return;
+  const bool cg = a.finest && a.k >= 1;
+  if (cg && a.cgcg ? ended_before(a.sc, a.k) : a.sc->done != 0) return;
   const int nx = a.Lf.n[0], ny = a.Lf.n[1];
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   const int gx0 = (tile % a.tiles_x) * TXT - H, gy0 = (tile / a.tiles_x) * TYT - H;
@@ -298,7 +299,6 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
   const bool fast = frame_interior(a.B, gx0, gy0, W, HH, nx, ny);
   const bool whole = gx0 + H + TXT <= nx && gy0 + H + TYT <= ny;
   double alpha = 0.0, beta = 0.0;
-  const bool cg = a.finest && a.k >= 1;
   if (cg && a.cgcg) {
     // gamma = r.u, delta = (A u).u, rr = r.r of iteration k-1: convergence
     // test, then alpha and beta of the single-reduction recurrence
@@ -319,9 +319,9 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
       a.sc->cc = cc;
       a.sc->iters = a.k - 1;
       if (conv || broken) {
-        a.sc->done = 1;
         a.sc->zero = (cc == 0.0);
         a.sc->nonconv = broken && !conv;
+        a.sc->done = a.k + 1;
       }
     }
     if (conv || broken) return;

@@ -383,14 +383,25 @@ __global__ void __launch_bounds__(kBlock) k_fold_partials(const double *in, long
   if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
+// Whether the solve ended before the kernel that makes the test of step k.
+// Its block 0 sets sc->done while other blocks are starting, so done is
+// k + 1, not merely nonzero: a block that starts late still makes the test
+// itself, with every wavefront. (With a plain flag the wavefronts of one
+// block can read it on either side of the store, and those that go on would
+// add up the partials without the others' shares.)
+__device__ inline bool ended_before(const SolverScalars *sc, int k) {
+  const int done = sc->done;
+  return done && done != k + 1;
+}
+
 // Convergence test on r_{k-1}; beta_k; p_k = z_{k-1} + beta_k p_{k-1};
 // q = L p_k; partials of p_k.q.
 template <int DIM, typename TZ>
 __global__ void __launch_bounds__(kBlock) k_cg_pq(CGArgs a, int np_cc) {
   __shared__ double sh[kBlock / 64];
   SolverScalars *sc = a.sc;
-  if (sc->done) return;
   const int k = a.k;
+  if (ended_before(sc, k)) return;
   double cc, rz, rr, rzo;
   sum_cc3(k, a.part_cc, np_cc, sc, a.part_rz, a.part_rz + a.np_rz, a.flexible ? a.part_rz + 2 * a.np_rz : nullptr,
           a.np_rz, cc, rz, rr, rzo);
@@ -404,9 +415,9 @@ __global__ void __launch_bounds__(kBlock) k_cg_pq(CGArgs a, int np_cc) {
     sc->cc = cc;
     sc->iters = k - 1;
     if (converged || broken) {
-      sc->done = 1;
       sc->zero = (cc == 0.0);
       sc->nonconv = broken && !converged;
+      sc->done = k + 1;
     }
   }
   if (converged || broken) return;
@@ -507,13 +518,11 @@ struct CgScalars {
   double alpha, beta, alpha_old;
   bool end, pending;  // the solve ends with this test; x lacks alpha_{k-1} p_{k-1}
 };
-// False: the solve was done before this kernel. sc->done is k + 1 when the
-// test of step k ended it: blocks that start after block 0 has set it still
-// take part.
+// False: the solve was done before this kernel.
 __device__ inline bool cgcg_scalars(const CGArgs &a, int np_cc, CgScalars &q) {
   SolverScalars *sc = a.sc;
-  const int k = a.k, done = sc->done;
-  if (done && done != k + 1) return false;
+  const int k = a.k;
+  if (ended_before(sc, k)) return false;
   double cc, g, d, rr;
   sum_cc3(k, a.part_cc, np_cc, sc, a.part_rz, a.part_rz + a.np_rz, a.part_rz + 2 * a.np_rz, a.np_rz, cc, g, d, rr);
   const bool conv = (cc == 0.0) || (rr <= a.tol2 * cc);

@@ -136,3 +136,23 @@ def test_cg_update_3d(n, bc, precision):
 @pytest.mark.parametrize("n", [(704, 608), (640, 640), (768, 512), (640, 512)], ids=str)
 def test_finest_tile_size(n, bc, precision):
     _check(n, bc, precision, rtol=1e-10)
+
+
+# grids of several thousand finest tiles or cell blocks, which start while
+# the first one ends the solve: the same solution to the last bit each time
+@pytest.mark.parametrize("precision", ["fp64", "mixed-flexible"])
+@pytest.mark.parametrize("n,bc", [((4096, 1024), None), ((2048, 2048), WALLS)], ids=["periodic", "walls"])
+def test_large_solve_is_reproducible(n, bc, precision):
+    import torch
+    from paper_2603_01727_amd import Solver
+    bc = None if bc is None else bc[:2]
+    s = Solver(n, (1.0, n[1] / n[0]), bc=bc, Re=10.0, dt=1e-3, precision=precision, poisson_rtol=1e-10)
+    b = torch.randn(n[1], n[0], dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(9))
+    print("reproducible", n, bc, precision, flush=True)
+    first, info = s.project(b)
+    first = first.clone()
+    assert info["relres"] <= 1e-10
+    for _ in range(6):
+        again, info2 = s.project(b)
+        assert info2 == info and torch.equal(again, first)
+    s.close()
