@@ -552,9 +552,8 @@ __device__ inline bool cgcg_scalars(const CGArgs &a, int np_cc, CgScalars &q) {
   return true;
 }
 
-// Any sides, variable coefficients: one thread per cell of a grid-stride
-// loop.
-template <int DIM, typename TZ>
+// 2D: one thread per cell of a grid-stride loop.
+template <typename TZ>
 __global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc) {
   CgScalars q;
   if (!cgcg_scalars(a, np_cc, q) || (q.end && !q.pending)) return;
@@ -571,9 +570,9 @@ __global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc) {
     auto pv = [&](long m) -> double { return old ? (double)u[m] + q.beta * a.pold[m] : (double)u[m]; };
     const double pc = pv(c);
     double nbs = 0.0, dg = 0.0;
-    const int x[3] = {i, j, kk};
+    const int x[2] = {i, j};
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
+    for (int d = 0; d < 2; ++d) {
       const long lo = nbr(a.L, a.B, c, x[d], d, -1), hi = nbr(a.L, a.B, c, x[d], d, +1);
       double s = 0.0, sb = 0.0;
       if (lo >= 0) {
@@ -595,17 +594,25 @@ __global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc) {
   }
 }
 
-// Periodic 3D, beta = 1: a block owns a 64 x 8 column of cells and marches
-// up a run of planes. Each thread keeps its column's p of three planes in
-// registers; the x and y neighbours come from an LDS plane (with a one-cell
-// ring) filled one plane ahead; the loads run two planes ahead. Every array
-// is read once but for the rings (28 % of u and p, from L2). Positions past
-// the far sides are copies of the cells they wrap to, and not written.
+// 3D: a block owns a 64 x 8 column of cells and marches up a run of planes.
+// Each thread keeps its column's p of three planes in registers; the x and y
+// neighbours come from an LDS plane (with a one-cell ring) filled one plane
+// ahead; the loads run two planes ahead. Every array is read once but for
+// the rings (28 % of u and p, from L2). Positions past the far sides are
+// copies of the cells they wrap to, and not written.
+// FORM 0: periodic, beta = 1; 1: any sides, beta = 1; 2: any sides, beta =
+// 1/rho_f (the density goes the way of p, 8 B per cell more). A face of a
+// side that is not periodic has the coefficient 0. 256^3, walls: 144 us
+// (FP64), 129 us (mixed), with a density 186 us; the same update with one
+// thread per cell of a grid-stride loop, its neighbours read from L2: 339,
+// 442 and 499 us; with s = A p carried, 231 us.
 constexpr int kUX = 64, kUY = 8, kUW = kUX + 2;
 constexpr int kURing = 2 * kUX + 2 * kUY;  // ring cells: two rows, two columns (no corners)
-template <typename TZ>
+template <typename TZ, int FORM>
 __global__ void __launch_bounds__(kUX *kUY, 4) k_cgcg_march(CGArgs a, int np_cc, int tiles_x, int tiles_y, int tz) {
+  constexpr bool VC = FORM == 2;
   __shared__ double P[2][(kUY + 2) * kUW];
+  __shared__ double Q[VC ? 2 : 1][VC ? (kUY + 2) * kUW : 1];
   CgScalars q;
   if (!cgcg_scalars(a, np_cc, q) || (q.end && !q.pending)) return;
   const Lay &L = a.L;
@@ -638,6 +645,15 @@ __global__ void __launch_bounds__(kUX *kUY, 4) k_cgcg_march(CGArgs a, int np_cc,
   const long rcol = ring ? L.base + (x0 + rx + nx) % nx + (long)((y0 + ry + ny) % ny) * L.s[1] : col;
   const int me = (ly + 1) * kUW + lx + 1, mr = (ry + 1) * kUW + rx + 1;
   const double ihx = a.ih2[0], ihy = a.ih2[1], ihz = a.ih2[2], dg = 2.0 * (ihx + ihy + ihz);
+  // FORM > 0: 1/h^2 of the cell's low and high faces along x and y, 0
+  // through a side
+  double fx0 = ihx, fx1 = ihx, fy0 = ihy, fy1 = ihy;
+  if constexpr (FORM != 0) {
+    if (!a.B.periodic[0] && x0 + lx == 0) fx0 = 0.0;
+    if (!a.B.periodic[0] && x0 + lx + 1 >= nx) fx1 = 0.0;
+    if (!a.B.periodic[1] && y0 + ly == 0) fy0 = 0.0;
+    if (!a.B.periodic[1] && y0 + ly + 1 >= ny) fy1 = 0.0;
+  }
   auto plane = [&](int z) __attribute__((always_inline)) { return (long)(z < 0 ? z + nz : (z >= nz ? z - nz : z)) * s2; };
   auto pv = [&](TZ uv, double po) __attribute__((always_inline)) { return (double)uv + (old ? q.beta * po : 0.0); };
   // p below, at and above the first plane; its ring; the old p of the centre
@@ -649,37 +665,75 @@ __global__ void __launch_bounds__(kUX *kUY, 4) k_cgcg_march(CGArgs a, int np_cc,
   double rv = a.rold[col + g0], xv = q.pending ? a.x[col + g0] : 0.0;
   TZ ur = TZ(0);
   double pr = 0.0;
+  // densities likewise: below, at and above the plane; the next plane's ring
+  double dm = 0.0, dc = 0.0, dn = 0.0, dr = 0.0;
+  if constexpr (VC) {
+    dm = a.rho[col + gm];
+    dc = a.rho[col + g0];
+    dn = a.rho[col + g1];
+    Q[z0 & 1][me] = dc;
+  }
   P[z0 & 1][me] = pc;
   if (ring) {
     P[z0 & 1][mr] = pv(u[rcol + g0], old ? a.pold[rcol + g0] : 0.0);
     ur = u[rcol + g1];
     pr = old ? a.pold[rcol + g1] : 0.0;
+    if constexpr (VC) {
+      Q[z0 & 1][mr] = a.rho[rcol + g0];
+      dr = a.rho[rcol + g1];
+    }
   }
   __syncthreads();
   for (int z = z0; z < z1; ++z) {
     // values of plane z + 1 in hand; those of z + 2 (and r, x of z + 1) in flight
     const double pp = pv(un, pn), pon = pn, pring = pv(ur, pr);
-    const double rc = rv, xc = xv;
+    const double rc = rv, xc = xv, dp = dn, dring = dr;
     const long g2 = plane(z + 2), gn = plane(z + 1), gz = (long)z * s2;
     if (z + 1 < z1) {
       un = u[col + g2];
       pn = old ? a.pold[col + g2] : 0.0;
       rv = a.rold[col + gn];
       xv = q.pending ? a.x[col + gn] : 0.0;
+      if constexpr (VC) dn = a.rho[col + g2];
       if (ring) {
         ur = u[rcol + g2];
         pr = old ? a.pold[rcol + g2] : 0.0;
+        if constexpr (VC) dr = a.rho[rcol + g2];
       }
     }
     const double *S = P[z & 1];
-    const double nbs = ihx * (S[me - 1] + S[me + 1]) + ihy * (S[me - kUW] + S[me + kUW]) + ihz * (pm + pp);
+    double Ap;
+    if constexpr (FORM == 0) {
+      const double nbs = ihx * (S[me - 1] + S[me + 1]) + ihy * (S[me - kUW] + S[me + kUW]) + ihz * (pm + pp);
+      Ap = dg * pc - nbs;
+    } else {
+      double cx0 = fx0, cx1 = fx1, cy0 = fy0, cy1 = fy1;
+      double cz0 = a.B.periodic[2] || z > 0 ? ihz : 0.0, cz1 = a.B.periodic[2] || z + 1 < nz ? ihz : 0.0;
+      if constexpr (VC) {
+        const double *D = Q[z & 1];
+        cx0 *= face_beta<double>(dc, D[me - 1]);
+        cx1 *= face_beta<double>(dc, D[me + 1]);
+        cy0 *= face_beta<double>(dc, D[me - kUW]);
+        cy1 *= face_beta<double>(dc, D[me + kUW]);
+        cz0 *= face_beta<double>(dc, dm);
+        cz1 *= face_beta<double>(dc, dp);
+      }
+      const double nbs = (cx0 * S[me - 1] + cx1 * S[me + 1]) + (cy0 * S[me - kUW] + cy1 * S[me + kUW]) + (cz0 * pm + cz1 * pp);
+      Ap = ((cx0 + cx1) + (cy0 + cy1) + (cz0 + cz1)) * pc - nbs;
+    }
     if (own) {
       a.pnew[col + gz] = pc;
-      a.rnew[col + gz] = rc - q.alpha * (dg * pc - nbs);
+      a.rnew[col + gz] = rc - q.alpha * Ap;
       if (q.pending) a.x[col + gz] = xc + (q.alpha_old * po + q.alpha * pc);
     }
     P[(z + 1) & 1][me] = pp;
     if (ring) P[(z + 1) & 1][mr] = pring;
+    if constexpr (VC) {
+      Q[(z + 1) & 1][me] = dp;
+      if (ring) Q[(z + 1) & 1][mr] = dring;
+      dm = dc;
+      dc = dp;
+    }
     __syncthreads();
     pm = pc;
     pc = pp;
@@ -1786,7 +1840,8 @@ static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k, Part part)
       hipEvent_t e0 = nullptr, e1 = nullptr;
       const bool timed = part != kTail && timed_launch(ws, 2, e0, e1);
       if (part != kTail) {
-        if (DIM == 3 && ws.bnd.all_periodic && !ws.vc) {
+        auto upd = &k_cgcg_update<T>;
+        if (DIM == 3) {
           // a run of planes per block: about four blocks of eight wavefronts
           // per compute unit, at least 8 planes (two more are read)
           const Lay &L = ws.lay;
@@ -1794,14 +1849,15 @@ static void iteration(hipStream_t st, PoissonWS &ws, CGArgs a, int k, Part part)
           const int nch = std::max(1, 1024 / (tx * ty));
           const int tz = std::max(8, tiles_along(L.n[2], nch));
           const dim3 g(tx * ty * tiles_along(L.n[2], tz)), b(kUX * kUY);
+          auto march = ws.vc ? &k_cgcg_march<T, 2> : (ws.bnd.all_periodic ? &k_cgcg_march<T, 0> : &k_cgcg_march<T, 1>);
           if (timed)
-            hipExtLaunchKernelGGL(k_cgcg_march<T>, g, b, 0, st, e0, e1, 0, a, kRedBlocks, tx, ty, tz);
+            hipExtLaunchKernelGGL(march, g, b, 0, st, e0, e1, 0, a, kRedBlocks, tx, ty, tz);
           else
-            hipLaunchKernelGGL(k_cgcg_march<T>, g, b, 0, st, a, kRedBlocks, tx, ty, tz);
+            hipLaunchKernelGGL(march, g, b, 0, st, a, kRedBlocks, tx, ty, tz);
         } else if (timed) {
-          hipExtLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, e0, e1, 0, a, kRedBlocks);
+          hipExtLaunchKernelGGL(upd, dim3(kRedBlocks), dim3(kBlock), 0, st, e0, e1, 0, a, kRedBlocks);
         } else {
-          hipLaunchKernelGGL((k_cgcg_update<DIM, T>), dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks);
+          hipLaunchKernelGGL(upd, dim3(kRedBlocks), dim3(kBlock), 0, st, a, kRedBlocks);
         }
       }
       if (timed) ws.tk[ws.tcount++] = k;

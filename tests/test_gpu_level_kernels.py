@@ -156,3 +156,13 @@ def test_large_solve_is_reproducible(n, bc, precision):
         again, info2 = s.project(b)
         assert info2 == info and torch.equal(again, first)
     s.close()
+
+
+# 3D CG update with a density: columns of 72 = 64 + 8 cells, rows of 12 = 8 + 4
+# and 28 = 3 * 8 + 4, faces of periodic and other sides, coarsest levels of
+# at most 128 cells
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("bc", [None, WALLS, OPEN], ids=["periodic", "walls", "open"])
+@pytest.mark.parametrize("n", [(72, 24, 16), (24, 12, 28), (12, 28, 24)], ids=str)
+def test_cg_update_3d_density(n, bc, precision):
+    _check(n, bc, precision, density=True)
