@@ -5,8 +5,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <functional>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/lowmach.h"
@@ -369,6 +369,20 @@ hipError_t poisson_setup(hipStream_t st, PoissonWS &ws, const double h[3]);
 // Gauss-Jordan in LDS); needs a coarsest level of <= kVcCoarsest cells
 // (hipErrorInvalidValue otherwise).
 hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws);
+// The work queued behind a solve: a reference to the caller's callable, which
+// outlives the call. It owns nothing, so making one cannot fail (a
+// std::function of a lambda with more than two captures allocates, and its
+// bad_alloc would leave through the C functions).
+struct AfterSolve {
+  hipError_t (*call)(void *) = nullptr;
+  void *obj = nullptr;
+  AfterSolve() = default;
+  template <typename F, typename = std::enable_if_t<!std::is_same<std::remove_cv_t<F>, AfterSolve>::value>>
+  AfterSolve(F &f) noexcept : call([](void *o) { return (*static_cast<F *>(o))(); }), obj(&f) {}
+  explicit operator bool() const { return call != nullptr; }
+  hipError_t operator()() const { return call(obj); }
+};
+static_assert(std::is_trivially_copyable<AfterSolve>::value, "AfterSolve owns nothing");
 // Solve A x = b for the zero-mean x (A P = sum_d delta_1 delta_1 P with
 // zero-flux non-periodic sides), warm-started from x0 (NULL = 0). b is read
 // with sc->mean_b and the outflow shift sc->outflow_c removed on the fly.
@@ -381,7 +395,7 @@ hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws);
 // so its kernels run only when solved(sc) holds (they take sc as their gate).
 hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const double *x0, double rtol,
                          int maxit, int expect_iters, int *iters, double *relres, int *converged,
-                         SolveLog *log = nullptr, const std::function<hipError_t()> &after = nullptr);
+                         SolveLog *log = nullptr, AfterSolve after = {});
 // Prepares a variable-coefficient solve from the density in ws.rho64 (fine
 // layout): the density on every level (2^d-cell averages), the coarse
 // levels' face coefficients and the coarsest pseudo-inverse. Sets

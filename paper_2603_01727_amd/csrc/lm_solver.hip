@@ -1912,7 +1912,7 @@ static hipError_t await_scalars(hipStream_t st, PoissonWS &ws) {
 template <int DIM, typename T>
 static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec, const double *x0, double rtol,
                               int maxit, int *iters, double *relres, int *converged, SolveLog *log,
-                              const std::function<hipError_t()> &after) {
+                              AfterSolve after) {
   BlockPCGArgs<T> pa;
   pa.ca = coarse_args<T>(ws, ws.z[0], ws.r[0]);
   pa.L = ws.lay;
@@ -1957,7 +1957,7 @@ static hipError_t solve_block(hipStream_t st, PoissonWS &ws, const double *bvec,
 template <int DIM, typename T>
 static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, const double *x0, double rtol,
                             int maxit, int expect, int *iters, double *relres, int *converged, SolveLog *log,
-                            const std::function<hipError_t()> &after) {
+                            AfterSolve after) {
   if (ws.block_pcg) return solve_block<DIM, T>(st, ws, bvec, x0, rtol, maxit, iters, relres, converged, log, after);
   if (log) return hipErrorInvalidValue;
   CGArgs a;
@@ -2035,7 +2035,7 @@ static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, c
 
 hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const double *x0, double rtol,
                          int maxit, int expect_iters, int *iters, double *relres, int *converged, SolveLog *log,
-                         const std::function<hipError_t()> &after) {
+                         AfterSolve after) {
   const bool three = ws.lay.ndim == 3;
   auto solve = ws.mixed ? (three ? &solve_dim<3, float> : &solve_dim<2, float>)
                         : (three ? &solve_dim<3, double> : &solve_dim<2, double>);
