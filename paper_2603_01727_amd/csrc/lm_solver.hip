@@ -2002,7 +2002,7 @@ static hipError_t solve_dim(hipStream_t st, PoissonWS &ws, const double *bvec, c
   // flag. Too few iterations cost an empty pass of the gated kernels; one
   // iteration too many would cost its nine or more launches (2 us each).
   int k = 1;
-  int batch = expect > 0 ? expect : std::max(2, (int)(-0.7 * std::log10(rtol) + 0.5));
+  int batch = expect > 0 ? expect : (int)std::max(2.0, -0.7 * std::log10(rtol) + 0.5);
   for (int pass = 0;; ++pass) {
     for (int q = 0; q < batch && k <= maxit; ++q, ++k) iteration<DIM, T>(st, ws, a, k, kWhole);
     iteration<DIM, T>(st, ws, a, k, kHead);

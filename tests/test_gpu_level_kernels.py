@@ -166,3 +166,23 @@ def test_large_solve_is_reproducible(n, bc, precision):
 @pytest.mark.parametrize("n", [(72, 24, 16), (24, 12, 28), (12, 28, 24)], ids=str)
 def test_cg_update_3d_density(n, bc, precision):
     _check(n, bc, precision, density=True)
+
+
+# tolerances from none at all (the zero start passes) to one that only the
+# iteration limit ends: the count of iterations queued before the outcome is
+# read stays a number
+@pytest.mark.parametrize("rtol,iters", [(math.inf, 0), (2.0, 0), (1e-320, None)], ids=str)
+@pytest.mark.parametrize("n", [(96, 80), (24, 20, 32)], ids=str)
+def test_extreme_tolerances(n, rtol, iters):
+    from paper_2603_01727_amd import LowMachError, Solver, lib
+    s = Solver(n, (1.0,) * len(n), Re=10.0, dt=1e-3, poisson_rtol=1e-10, poisson_maxit=12)
+    b = np.random.default_rng(5).standard_normal(tuple(reversed(n)))
+    print("tolerance", n, rtol, flush=True)
+    if iters is None:
+        with pytest.raises(LowMachError) as e:
+            s.project(b, rtol=rtol)
+        assert e.value.status == lib.LM_ENOCONV
+    else:
+        P, info = s.project(b, rtol=rtol)
+        assert info["iters"] == iters and not P.any()
+    s.close()
