@@ -1879,7 +1879,7 @@ extern "C" lm_status lm_project_static(const lm_grid *grid, const lm_params *par
   for (int d = 0; d < 3; ++d) h[d] = d < grid->ndim ? grid->L[d] / grid->n[d] : 1.0;
   // sizing pass: rejected before any device work when it does not fit
   PoissonWS ws{};
-  ws.geo_given = 1;
+  ws.fixed = 1;
   double *b = nullptr, *staging = nullptr;
   Carver sz{nullptr, 0};
   if (!carve_solve(ws, sz, L, B, h, *params, &b, &staging))
@@ -1908,7 +1908,7 @@ extern "C" lm_status lm_project_static(const lm_grid *grid, const lm_params *par
   }
   hipStream_t st = (hipStream_t)stream;
   ws = PoissonWS{};
-  ws.geo_given = 1;
+  ws.fixed = 1;
   ws.geo = base + kScratchBytes;
   Carver cv{(char *)base, 0};
   carve_solve(ws, cv, L, B, h, *params, &b, &staging);

@@ -325,11 +325,12 @@ struct PoissonWS {
   int mixed, nu;
   MGLevel lev[kMaxLev];    // level 0 uses r, zpre and z below
   int tx[kMaxLev], ty[kMaxLev];  // 2D tile of the fused level kernels (0: level not tiled)
-  double *x, *r[2], *p[2], *q;
+  double *x, *r[2], *p[2];
+  double *q;               // A p (flexible CG; else NULL)
   int cgcg;                // single-reduction (Chronopoulos-Gear) CG in FP64 mode
   int block_pcg;           // the whole solve in one workgroup (finest level <= kCoarseCells)
   double tol2;             // rtol^2 of the solve in progress
-  double *w, *s[2];        // its A u and s = A p vectors
+  double *w, *s[2];        // its A u and s = A p vectors (2D tiles; else NULL)
   void *z[2];              // preconditioned residuals in MG precision
   void *zpre;              // finest-level pre-smoothed correction
   void *pinv;              // dense pseudo-inverse of the coarsest operator
@@ -347,7 +348,10 @@ struct PoissonWS {
   double *rho64;           // finest-level density (FP64, fine layout)
   void *rho[kMaxLev];      // density per level in MG precision (level 0 aliases rho64 in FP64)
   void *geo = nullptr;     // block geometry of the coarse-kernel levels (kGeoBytes)
-  int geo_given = 0;       // geo is the caller's, not carved
+  // a solve in scratch of a fixed size: geo is the caller's, and q, w and s
+  // are carved for every grid, so that the grids the scratch takes do not
+  // depend on which kernels they run
+  int fixed = 0;
   void *ccf;               // face coefficients of the coarse-kernel levels, by block (MG precision)
   double *ccd;             // those of the finest level in FP64 (one-workgroup solve, mixed precision)
   void *pinv_vc;           // pseudo-inverse of the coarsest variable-coefficient operator

@@ -1204,8 +1204,23 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
   ws.r[1] = (double *)cv.take(fbytes);
   ws.p[0] = (double *)cv.take(fbytes);
   ws.p[1] = (double *)cv.take(fbytes);
-  ws.q = (double *)cv.take(fbytes);
   ws.cgcg = !flexible;
+  // 2D tiles
+  for (int l = 0; l < kMaxLev; ++l) {
+    ws.tx[l] = ws.ty[l] = 0;
+    ws.vtx[l] = ws.vty[l] = 0;
+    if (l < nl) {
+      choose_tile(ws, l);
+      choose_tile_vc(ws, l);
+    }
+  }
+  // only flexible CG stores q = A p, and only the single-reduction form on 2D
+  // tiles w = A u and s = A p
+  const bool tiled = ws.tx[0] > 0 || ws.vtx[0] > 0;
+  ws.q = flexible || ws.fixed ? (double *)cv.take(fbytes) : nullptr;
+  ws.w = ws.s[0] = ws.s[1] = nullptr;
+  if ((ws.cgcg && tiled) || ws.fixed)
+    for (double **v : {&ws.w, &ws.s[0], &ws.s[1]}) *v = (double *)cv.take(fbytes);
   // grids the one-block V-cycle covers from the finest level: the whole
   // single-reduction solve in one workgroup (LM_BLOCK_PCG=0 turns it off)
   {
@@ -1213,9 +1228,6 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
     const bool off = env && env[0] == '0';
     ws.block_pcg = !off && ws.cgcg && ws.lc == 0 && fine.ncells() <= kCoarseCells;
   }
-  ws.w = (double *)cv.take(fbytes);
-  ws.s[0] = (double *)cv.take(fbytes);
-  ws.s[1] = (double *)cv.take(fbytes);
   ws.z[0] = cv.take((size_t)fine.total * eb);
   ws.z[1] = (mixed && !ws.cgcg) ? cv.take((size_t)fine.total * eb) : ws.z[0];  // z_old: flexible CG only
   ws.zpre = cv.take((size_t)fine.total * eb);
@@ -1229,7 +1241,7 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
     ws.lev[l].b = cv.take(lb);
   }
   ws.pinv = cv.take((size_t)ncoarsest * ncoarsest * eb);
-  if (!ws.geo_given) ws.geo = cv.take(kGeoBytes);
+  if (!ws.fixed) ws.geo = cv.take(kGeoBytes);
   ws.rho64 = nullptr;
   ws.ccf = ws.pinv_vc = nullptr;
   ws.ccd = nullptr;
@@ -1244,16 +1256,9 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
   }
   for (int l = 0; l < kMaxLev; ++l)
     for (int q = 0; q < 3; ++q) ws.cf[l][q] = nullptr;
-  for (int l = 0; l < kMaxLev; ++l) {
-    ws.tx[l] = ws.ty[l] = 0;
-    ws.vtx[l] = ws.vty[l] = 0;
-    if (l < nl) {
-      choose_tile(ws, l);
-      choose_tile_vc(ws, l);
-    }
+  for (int l = 0; l < nl; ++l)
     if (ws.vtx[l] > 0)
       for (int q = 0; q < 3; ++q) ws.cf[l][q] = cv.take((size_t)ws.lev[l].lay.total * eb);
-  }
   long npmax = kRedBlocks;
   if (ws.tx[0] > 0) npmax = std::max(npmax, (long)tiles2d(fine, ws.tx[0], ws.ty[0]) + 1);
   if (ws.vtx[0] > 0) npmax = std::max(npmax, (long)tiles2d(fine, ws.vtx[0], ws.vty[0]) + 1);
@@ -2180,7 +2185,8 @@ static hipError_t bench_launch_dim(hipStream_t st, PoissonWS &ws, int which) {
   a.rnew = ws.r[1];
   a.pold = ws.p[0];
   a.pnew = ws.p[1];
-  a.q = ws.q;
+  // (where A p is not stored: a vector that the kernel does not use otherwise)
+  a.q = ws.q ? ws.q : (which == 2 ? ws.r[1] : ws.p[0]);
   a.z = ws.z[0];
   a.zold = nullptr;
   a.part_cc = ws.part_cc;

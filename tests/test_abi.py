@@ -251,3 +251,22 @@ def test_stretched_grid_checks_without_gpu():
     assert size(g, p, [f, f]) == lib.LM_EUNSUPPORTED
     p.p0_closed = 0
     assert size(g, p, [f, f]) == lib.LM_OK
+
+
+def test_workspace_holds_only_the_vectors_its_solver_uses():
+    """q = A p belongs to flexible CG; w = A u and s = A p to the
+    single-reduction form on 2D tiles (mg_nu = 4 runs without tiles)."""
+    from paper_2603_01727_amd import lib
+    L = lib.load()
+
+    def size(n, precision=lib.LM_FP64, nu=2):
+        g, p = _grid_params(n)
+        p.precision, p.mg_nu = precision, nu
+        b = C.c_size_t()
+        assert L.lm_workspace_size(C.byref(g), C.byref(p), C.byref(b)) == lib.LM_OK
+        return b.value
+
+    N = 128 ** 3  # q and, of the 4-byte preconditioner, the z before the last
+    assert size((128,) * 3, lib.LM_MIXED_FLEXIBLE) - size((128,) * 3, lib.LM_MIXED) >= (8 + 4) * N
+    N = 1024 ** 2  # w and two of s
+    assert size((1024, 1024)) - size((1024, 1024), nu=4) >= 3 * 8 * N

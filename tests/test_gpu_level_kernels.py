@@ -186,3 +186,27 @@ def test_extreme_tolerances(n, rtol, iters):
         P, info = s.project(b, rtol=rtol)
         assert info["iters"] == iters and not P.any()
     s.close()
+
+
+# the timing hook on grids that store A p (flexible CG) and that do not: every
+# class still runs, on vectors of its own, and the next solve is unharmed
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "mixed-flexible"])
+@pytest.mark.parametrize("n", [(96, 80), (24, 20, 32)], ids=str)
+def test_kernel_timing_hook(n, precision):
+    import ctypes as C
+    import torch
+    from paper_2603_01727_amd import Solver
+    s = Solver(n, (1.0,) * len(n), Re=10.0, dt=1e-3, precision=precision)
+    one = torch.ones(tuple(reversed(n)), dtype=torch.float64, device="cuda")
+    s.set(T=one, v=[one * 0.0] * len(n))
+    b = torch.randn(one.shape, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    before, _ = s.project(b)
+    before = before.clone()
+    for which in range(8):
+        print("hook", n, precision, which, flush=True)
+        ms = C.c_double(-1.0)
+        assert s.lib.lm_bench_kernel(s.ctx, which, 2, C.byref(ms)) == 0
+        assert ms.value > 0.0
+    after, _ = s.project(b)
+    assert torch.equal(before, after)
+    s.close()
