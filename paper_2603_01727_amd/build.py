@@ -22,10 +22,11 @@ HIPCC_FLAGS = [
 ]
 
 
-# The adjoint's residual gather evaluates dual numbers whose derivative
-# parts are constant zeros wherever a stencil position is not the seeded
-# cell; folding 0 * x and 0 + x away (no NaN / infinity operands, signed
-# zeros immaterial) removes that arithmetic. Values stay finite there.
+# The adjoint's residual transpose in the band along sides evaluates dual
+# numbers whose derivative parts are constant zeros wherever a stencil
+# position is not the seeded cell; folding 0 * x and 0 + x away (no NaN /
+# infinity operands, signed zeros immaterial) removes that arithmetic. The
+# closed form away from sides has no such zeros; both work on finite values.
 SOURCE_FLAGS = {"lm_adjoint.hip": ["-ffinite-math-only", "-fno-signed-zeros"]}
 
 

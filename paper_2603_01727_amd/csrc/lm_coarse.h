@@ -19,11 +19,11 @@
 // What bounds it: latency (one workgroup; about 30 dependent phases of one
 // LDS round trip and a few FP64 operations each), on the largest level the
 // LDS rate (six 8-byte accesses per thread and half-sweep). Measured, FP64:
-// a cycle from 64^2 as its own launch 11 us, the 64^2 solve of 8 iterations
-// 100 us. (Two cells of one colour per thread, found through index sets in
-// LDS with two-way bank conflicts, and the CG vectors in L2 scratch: 18 us
-// and 220 us; with variable coefficients, the face divisions redone in every
-// half-sweep, 37 us per cycle against 12 us, FP32.)
+// a cycle from 64^2 as its own launch 12.9 us, the 64^2 solve of 8 iterations
+// 101 us. (Two cells of one colour per thread, found through index sets in
+// LDS with two-way bank conflicts, and the CG vectors in L2 scratch: 20.4 us
+// and 203 us; with variable coefficients, the face divisions redone in every
+// half-sweep, 37 us per cycle against 13.8 us, FP32.)
 #pragma once
 
 namespace lm {

@@ -126,8 +126,8 @@ struct HostSolve {
   unsigned seq;
 };
 
-// Outcome of one pressure solve, written on the device when the host
-// checks it later (after the step) instead of waiting for it.
+// Outcome of one pressure solve, written by its kernel to pinned host memory
+// when the host checks it later (after the step) instead of waiting for it.
 struct SolveLog {
   double rr, cc, mean_b;
   int iters, done, nonconv, pad;
@@ -370,7 +370,7 @@ bool poisson_plan(PoissonWS &ws, Carver &cv, const Lay &fine, const Bnd &B, cons
 // the coarsest-level pseudo-inverse (after carving).
 hipError_t poisson_setup(hipStream_t st, PoissonWS &ws, const double h[3]);
 // The same with the pseudo-inverse built on the device (one block,
-// Gauss-Jordan in LDS); needs a coarsest level of <= kVcCoarsest cells
+// Gauss-Jordan in registers); needs a coarsest level of <= kVcCoarsest cells
 // (hipErrorInvalidValue otherwise).
 hipError_t poisson_setup_device(hipStream_t st, PoissonWS &ws);
 // The work queued behind a solve: a reference to the caller's callable, which
@@ -392,11 +392,13 @@ static_assert(std::is_trivially_copyable<AfterSolve>::value, "AfterSolve owns no
 // with sc->mean_b and the outflow shift sc->outflow_c removed on the fly.
 // The solution stays in ws.x with its mean in sc->mean_x. With log (only
 // when ws.block_pcg) the call returns once the solve is queued and its
-// outcome lands in *log on the device; iters, relres and converged are then
-// not written.
+// outcome lands in *log (pinned memory); iters, relres and converged are
+// then not written.
 // after (optional) queues the work that follows the solve on the stream; it
 // is queued before the host has read the outcome, possibly more than once,
-// so its kernels run only when solved(sc) holds (they take sc as their gate).
+// so its kernels take sc as their gate and run only when solved(sc) holds.
+// (With a log it is queued once, and a caller that voids what a failed solve
+// leaves may leave the gate out: lm_step's projection.)
 hipError_t poisson_solve(hipStream_t st, PoissonWS &ws, const double *b, const double *x0, double rtol,
                          int maxit, int expect_iters, int *iters, double *relres, int *converged,
                          SolveLog *log = nullptr, AfterSolve after = {});

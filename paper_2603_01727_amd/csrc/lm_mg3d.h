@@ -53,7 +53,8 @@ __device__ inline int wrap_p(int g, int n) {
   return r < 0 ? r + n : r;
 }
 // Plane index of the loads, which stay within [-n, 2n) on the fused levels
-// (chunks reach at most 13 planes past either end; levels have >= 16).
+// (a march reads at most 5 planes before its chunk and 7 past it; levels
+// have >= 16).
 __device__ inline int wrap_any(int g, int n) { return g < 0 ? g + n : (g >= n ? g - n : g); }
 
 // The pair's two right-hand-side values at offset g: FP64 (the finest
@@ -317,9 +318,9 @@ __global__ void __launch_bounds__(kF3Threads, 4) k_mg_down3d(Fused3DArgs<T> a) {
 // Stage s (1 .. 2 NU) runs at lag s. With EXTRA = 1 (finest level of the
 // FP64 single-reduction CG) a last stage at lag 2 NU + 1 forms w = A u on
 // the owned cells in FP64 with the partials of r.u, w.u and r.r (r = the
-// level's right-hand side, read in FP64; w itself is not needed again). Halo 2 NU + EXTRA planes in z; in x and y
-// rounded up to even, so the pairs sit on (even, odd) columns and never
-// straddle the periodic seam.
+// level's right-hand side, read in FP64; w itself is not needed again).
+// Halo 2 NU + EXTRA planes in z; in x and y rounded up to even, so the pairs
+// sit on (even, odd) columns and never straddle the periodic seam.
 template <typename T, int NU, int EXTRA, bool BD>
 __global__ void __launch_bounds__(kF3Threads, 4) k_mg_up3d(Fused3DArgs<T> a) {
   constexpr int S = 2 * NU;

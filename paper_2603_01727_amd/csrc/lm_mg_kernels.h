@@ -347,7 +347,6 @@ __global__ void __launch_bounds__(kBlock) k_mg_down2d(Down2DArgs<T> a) {
     gi[it] = ok[it] ? a.Lf.at(gx, gy, 0) : a.Lf.base;
   }
   if constexpr (VC) {
-    // densities on the whole frame (ring included), 0 for missing cells
     // coefficients on the whole frame (ring included), 0 for missing cells;
     // x starts at 0 everywhere (missing cells stay 0)
     T gv[NIT], fv[NIT], hv[NIT];

@@ -11,10 +11,11 @@
 // updates and dot products.
 //
 // CG. Single-reduction CG (Chronopoulos-Gear: one global reduction per
-// iteration, s = A p carried by recurrence and w = A u formed on the finest
-// level of the V-cycle) in FP64 and in the default mixed mode; flexible CG
-// (Polak-Ribiere beta, q = A p formed explicitly) in the flexible mixed
-// mode. Scalars never leave the device. A reduction kernel writes one
+// iteration) in FP64 and in the default mixed mode. On 2D tiles the V-cycle
+// stores w = A u on the finest level and s = A p is carried by recurrence;
+// elsewhere neither is stored and the update forms A p from p. Flexible CG
+// (Polak-Ribiere beta, q = A p stored) in the flexible mixed mode. Scalars
+// never leave the device. A reduction kernel writes one
 // partial sum per block; the next kernel that needs the total has every
 // block sum those partials in the same fixed order (no atomics, no grid-wide
 // fences, bitwise reproducible). The convergence test runs on the device and
@@ -22,14 +23,14 @@
 // host queues the expected iterations and reads the flag while the device
 // goes on with the work behind the solve, gated on its outcome.
 //
-// Levels. 2D levels run one LDS tile
+// Levels. 2D levels that a tile fits run one LDS tile
 // kernel per level and direction with temporal blocking (nu red-black sweeps
 // from a zero guess, residual and restriction on the way down; prolongation
 // and nu black-red sweeps on the way up; on the finest level also the CG
-// update, w = A u and the CG partial sums). Large fully periodic 3D levels
+// update, w = A u and the CG partial sums). Periodic 3D levels with beta = 1
 // run the z-marching equivalent (lm_mg3d.h). Levels of at most kCoarseCells
-// cells are solved by one block in LDS; the remaining levels run one kernel
-// per half-sweep.
+// cells are solved by one workgroup (lm_coarse.h); the remaining levels run
+// one kernel per half-sweep.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -512,8 +513,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_rz(CGArgs a) {
 // arrays to move; and x takes its update every second step, both directions
 // at once, when the old p is read anyway (x += alpha_{k-1} p_{k-1} +
 // alpha_k p_k on even steps, the pending one when the solve ends on an odd
-// one). 48 B per cell and step instead of 80: 256^3 FP64 168 us in step (4.8
-// TB/s, the rate of a large copy) instead of 257 us.
+// one). 48 B per cell and step instead of 80: 256^3 FP64 166 - 170 us in step
+// (4.7 - 4.8 TB/s) instead of 257 us.
 struct CgScalars {
   double alpha, beta, alpha_old;
   bool end, pending;  // the solve ends with this test; x lacks alpha_{k-1} p_{k-1}
@@ -602,10 +603,10 @@ __global__ void __launch_bounds__(kBlock) k_cgcg_update(CGArgs a, int np_cc) {
 // copies of the cells they wrap to, and not written.
 // FORM 0: periodic, beta = 1; 1: any sides, beta = 1; 2: any sides, beta =
 // 1/rho_f (the density goes the way of p, 8 B per cell more). A face of a
-// side that is not periodic has the coefficient 0. 256^3, walls: 144 us
-// (FP64), 129 us (mixed), with a density 186 us; the same update with one
-// thread per cell of a grid-stride loop, its neighbours read from L2: 339,
-// 442 and 499 us; with s = A p carried, 231 us.
+// side that is not periodic has the coefficient 0. 256^3, walls, mean over a
+// solve's iterations: 152 us (FP64), 135 us (mixed), with a density 190 us;
+// the same update with one thread per cell of a grid-stride loop, its
+// neighbours read from L2: 339, 442 and 499 us; with s = A p carried, 231 us.
 constexpr int kUX = 64, kUY = 8, kUW = kUX + 2;
 constexpr int kURing = 2 * kUX + 2 * kUY;  // ring cells: two rows, two columns (no corners)
 template <typename TZ, int FORM>
@@ -1068,6 +1069,10 @@ static void fit_tile(const Lay &L, int nu, const int (*cand)[2], int nc, int &tx
 // that the small one puts more wavefronts on a unit. FP64 solve, large and
 // small: 256^2 478 and 404 us, 512^2 599 and 529, 768 x 512 1268 and 1186,
 // 1024 x 512 2313 and 2308, 1024 x 768 1109 and 1216, 1024^2 840 and 1018.
+// Up to the line also in the other forms: mixed, 256^2 441 and 379, 512^2
+// 532 and 490, 768 x 512 785 and 774; with walls, FP64, 677 and 566, 833 and
+// 757, 1147 and 1063; mixed-flexible with walls 714 and 611, 874 and 788,
+// 1210 and 1115.
 constexpr int kLargeTiles = 384;
 
 static void choose_tile(PoissonWS &ws, int l) {

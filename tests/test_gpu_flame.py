@@ -42,8 +42,8 @@ def test_slot_flame_small(steps):
 
 
 def test_slot_flame_ragged_unfused():
-    """Sizes that are not tile multiples: every multigrid level takes the
-    per-half-sweep path, and the CG update runs in its own kernel."""
+    """Sizes that are not tile multiples (the last tiles reach past the
+    sides)."""
     case = c3_case(nx=80, ny=120, W=16, wall=4, wall_h=16, inj=4)
     print("slot flame 80x120", flush=True)
     o, st = oracle_for(case)

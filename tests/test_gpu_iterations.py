@@ -151,9 +151,9 @@ def _check(n, bc=None, nu=2, precision="fp64", density=False, stretch=0.0, apart
 
 PRECISIONS = ["fp64", "mixed", "mixed-flexible"]
 
-# one workgroup; whole tiles; edge tiles, the last just above the smallest
-# height a tile takes; too narrow for any tile; fused 3D levels, frames of
-# several periods; 3D with sides
+# one workgroup; whole tiles; edge tiles, the last too low for any but 32 x 8;
+# too narrow for any tile; fused 3D levels, frames of several periods; 3D
+# with sides
 ONE = [((64, 64), None), ((30, 22), WALLS), ((16, 16, 16), None), ((20, 12, 14), OPEN),
        ((128, 96), None), ((768, 512), WALLS), ((704, 608), None),
        ((88, 72), None), ((240, 176), WALLS), ((212, 20), OPEN),

@@ -77,8 +77,8 @@ def test_one_workgroup_cycle_density(n, bc, precision):
 
 
 # 2D levels that no tile divides: edge tiles past periodic and other sides,
-# a second ragged level, sides just above and below the smallest a tile
-# takes (the last runs the unfused kernels), one to four sweeps
+# a second ragged level, the last too low for any tile but 32 x 8, one to four
+# sweeps (four: no tiles)
 RAGGED = [(88, 72), (72, 88), (240, 176), (24, 208), (44, 100), (212, 20)]
 
 
@@ -120,8 +120,7 @@ def test_fused_3d_levels(n, nu, precision):
 
 # 3D CG update beyond the one-workgroup solve: periodic columns that do not
 # divide the grid in x or y, and the form for other sides; the coarsest
-# levels hold 540, 480 and 204 cells (dense inverse read in long and short
-# runs)
+# levels hold 540, 240 and 408 cells (dense inverse)
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("bc", [None, WALLS, OPEN], ids=["periodic", "walls", "open"])
 @pytest.mark.parametrize("n", [(72, 20, 24), (24, 20, 32), (136, 12, 16)], ids=str)

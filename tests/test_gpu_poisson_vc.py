@@ -33,7 +33,7 @@ def _solver(n, L, bc=None, precision="fp64", rtol=1e-13):
 
 
 # (n, L, bc): periodic tiled (32x8), two tiled levels, zero-flux sides with
-# 32x8 then 16x16 tiles, 16x16 only, an untiled finest level, 3D periodic
+# 32x8 then 16x16 tiles, 16x16 only, sizes that no tile divides, 3D periodic
 # and 3D with walls (per-half-sweep kernels), a grid solved by the coarse
 # kernel alone
 CASES = [
